@@ -5,7 +5,7 @@ FP32 accumulators; batch <= 8 FC layers use xor + popcount on the vector ALU.
 
 Every step of the path runs in the HIP kernels of libbnn.so; this package only marshals
 arguments.  There is no CPU fallback: importing the package raises if the shared library has
-not been built (python -m paper_2301_05126_amd.build).
+not been built (python paper_2301_05126_amd/build.py).
 """
 from . import api  # noqa: F401
 from . import runtime  # noqa: F401

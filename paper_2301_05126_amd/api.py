@@ -11,7 +11,7 @@ LIB_PATH = os.path.join(_HERE, "libbnn.so")
 
 if not os.path.exists(LIB_PATH):
     raise ImportError(
-        f"{LIB_PATH} is missing: build it with `python -m paper_2301_05126_amd.build` "
+        f"{LIB_PATH} is missing: build it with `python paper_2301_05126_amd/build.py` "
         "(there is no fallback path)")
 
 _lib = C.CDLL(LIB_PATH)
