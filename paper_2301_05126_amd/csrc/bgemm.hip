@@ -11,8 +11,8 @@
 // which changes a dot product.  Zero-filled words beyond K (and the zero tail bits of the
 // last word) count as matches, a constant that the epilogue subtracts.
 //
-//   bgemm_mfma<TM,TN>  block = 2x2 waves, wave tile (32*TM) x (32*TN), K streamed through
-//                      LDS as packed words in chunks of 16 .. 64 words.
+//   bgemm_mfma<TM,TN>  persistent blocks of 2x2 waves, wave tile (32*TM) x (32*TN), K streamed through
+//                      LDS as packed words in chunks of 16 words, across the block's tiles.
 //   bgemm_small        few 64 x 64 tiles: 32 x 32 outputs per block, K split over its four waves,
 //                      operands straight from global memory.
 //   bgemv_rows         m <= 8: bandwidth-bound, xor + popcount on the VALU, four output rows of
@@ -20,43 +20,19 @@
 // All end in the same epilogue: optional int32 store, optional threshold/flip/bit-pack.  The two
 // small-problem kernels can also carry the model's last layer (TAIL): each block adds the share
 // of its 32-bit output words to the logits.
+#include <mutex>
+
 #include "bnn_internal.h"
+#include "conv_epilogue.h"
+#include "lds_dma.h"
 
 namespace bnn {
 
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// Packed k-words per LDS chunk: small tiles take long chunks (fewer barriers per MFMA, their
-// launches are latency-bound), the 256 x 256 tile short ones (registers).
-constexpr int chunk_words(int tm, int tn) { return tm * tn >= 16 ? 16 : (tm * tn >= 4 ? 32 : 64); }
-
-
-template <int VEC>
-__device__ __forceinline__ uint4 load_row_words(const uint32_t *__restrict__ base, int64_t row,
-                                                int64_t rows, int kw_total, int kpos)
-{
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (row < rows) {
-        const uint32_t *p = base + row * (int64_t)kw_total + kpos;
-        if (VEC == 4) {
-            if (kpos < kw_total) v = *reinterpret_cast<const uint4 *>(p);
-        } else if (VEC == 2) {
-            if (kpos < kw_total) { uint2 t = *reinterpret_cast<const uint2 *>(p); v.x = t.x; v.y = t.y; }
-            if (kpos + 2 < kw_total) { uint2 t = *reinterpret_cast<const uint2 *>(p + 2); v.z = t.x; v.w = t.y; }
-        } else {
-            if (kpos < kw_total) v.x = p[0];
-            if (kpos + 1 < kw_total) v.y = p[1];
-            if (kpos + 2 < kw_total) v.z = p[2];
-            if (kpos + 3 < kw_total) v.w = p[3];
-        }
-    }
-    return v;
-}
-
-// The same four words without branches, so that many such loads can be in flight together: a
+// Four words of a row without branches, so that many such loads can be in flight together: a
 // word that does not exist reads the tensor's first word and is zeroed afterwards.
 template <int VEC>
 __device__ __forceinline__ uint4 load_row_words_nb(const uint32_t *__restrict__ base, int64_t row,
@@ -87,252 +63,373 @@ __device__ __forceinline__ uint4 load_row_words_nb(const uint32_t *__restrict__ 
     return v;
 }
 
-// 32 packed bits -> 32 FP4 values in the low four dwords of an MFMA operand.
-// FP4 E2M1: 0b0010 = +1.0, 0b1010 = -1.0; bit b of the word lands in nibble b/4 of dword 3 - b%4.
-// sgn / one hold 0x88888888 / 0x22222222 in registers so that each dword is one v_and_or_b32.
-__device__ __forceinline__ v8i expand_fp4(uint32_t w, uint32_t sgn, uint32_t one)
-{
-    v8i r;
-    r[0] = (int)(((w << 3) & sgn) | one);
-    r[1] = (int)(((w << 2) & sgn) | one);
-    r[2] = (int)(((w << 1) & sgn) | one);
-    r[3] = (int)((w & sgn) | one);
-    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;
-    return r;
-}
-
 __device__ __forceinline__ uint32_t word_of(const uint4 &v, int q)
 {
     return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w));
 }
 
-// Where a block's tile lies and when the block starts.
+// Makes a tile's accumulators opaque at this point, in the registers where they are: the compiler
+// would otherwise copy them all out of the accumulation registers at the end of the loop, and spill.
+__device__ __forceinline__ void pin_acc(v16f &acc) { asm volatile("" : "+a"(acc)); }
+
+// Tiles of the problem.
 struct GemmWalk {
     int nbm, nbn;            // tiles along M and N
-    unsigned stagger_ticks;  // start delays of the first 256 blocks are spread over this many 100 MHz ticks
+    int tiles;               // nbm * nbn
 };
 
-// One block per tile.  Tile numbers run column-major inside bands of eight tile rows, and the
-// blocks that hardware deals to one XCD (ids equal modulo 8) take neighbouring numbers, so the
-// tiles in flight on one L2 form a patch that shares rows of A and of B.
-template <int TM, int TN, int VEC>
-__global__ __launch_bounds__(256, 1) void bgemm_mfma(const uint32_t *__restrict__ A,
+// Persistent blocks.  Tile numbers run column-major inside bands of eight tile rows; each XCD takes
+// a contiguous eighth of them and its blocks (hardware deals block ids round-robin to the XCDs)
+// walk through it side by side, so the tiles in flight on one L2 form a patch that shares rows of A
+// and of B.
+//
+// K streams through four LDS buffers of KC = 16 words per row, filled by global -> LDS transfers
+// that bypass the registers and are requested three chunks ahead.  A chunk costs one barrier, in its
+// middle: there the next chunk is known to have landed for every wave and the previous one to be
+// consumed, so the first words of the next chunk are read, and its first operands expanded, behind
+// the last MFMAs of the current one.  The chunk sequence runs on across the block's tiles: the
+// first chunks of the next tile are in flight during the last ones of this tile and during its
+// epilogue, and the stores of a tile drain behind the first chunks of the next.
+//
+// What bounds it (256 x 256 tile): the MFMA pipe during the chunks, at 34.7 ticks per MFMA and SIMD of
+// the 32 that a lone wave reaches with its operands in registers (46 with two barriers per chunk
+// and staging through registers), and the power limit, which holds the clock at 1.9 GHz; then the
+// stores of raw sums, 256 KB per tile and compute unit, in which the matrix pipe idles (9.4 us
+// where all compute units store at once, the chip's write bandwidth; 5.7 us otherwise).  Before and
+// after, us: 16384^3 1592 / 1408, 8192^3 216 / 200, 4096^3 35.2 / 34.5 (a single round: 9.4 of its 34 us
+// are the stores), step output at 5000 x 5000 x 10000 194 / 107, 4096 x 1024 x 8192 19.3 / 14.7.
+//
+// An LDS row is four 16-byte units; unit u of row r sits at position u ^ ((r >> 1) & 3), so that the
+// eight rows which one phase of a 16-byte read touches fall into distinct bank groups.  (A transfer
+// writes 1 KB linearly; which unit a lane fetches makes the arrangement.)  Rows past M or N and
+// words past K address past the end of the tile's buffer resource and arrive as zeros.
+// VEC: 4 when rows are a whole number of 16-byte units, else 1 (four-byte transfers).
+//
+// B is the MFMA's first matrix: accumulator register r of lane (l32, half) is column 8(r/4) + 4*half +
+// r%4 of a 32 x 32 tile and row l32, i.e. four neighbouring columns at a time: raw sums leave as
+// 16-byte stores, and the step needs two instructions per value (see conv_epilogue.h).
+constexpr int KC = 16, NBUF = 4, XW = 32 * 32;
+
+// RAW / PACKED: which outputs the instance writes (one of the two in all but diagnostic calls).
+template <int TM, int TN, int VEC, int OCC, bool RAW, bool PACKED>
+__global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restrict__ A,
                                                       const uint32_t *__restrict__ B, int64_t M, int64_t N,
                                                       int Kw, int K, GemmWalk gw, EpiArgs ep)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;     // 2 x 2 waves
-    constexpr int KC = chunk_words(TM, TN);
-    constexpr int LS = KC + 4;    // LDS row stride in words; LS/4 odd -> 16-byte reads of
-                                  // consecutive rows fall into distinct bank groups
-    constexpr int UPR = KC / 4, SA = BM * UPR / 256, SB = BN * UPR / 256;   // staging units
-    constexpr int NG = KC / 8, NST = KC / 2;      // 8-word groups and MFMA steps per chunk
-    __shared__ __align__(16) uint32_t As[BM * LS];
-    __shared__ __align__(16) uint32_t Bs[BN * LS];
+    constexpr int IA = VEC == 4 ? TM : 4 * TM, IB = VEC == 4 ? TN : 4 * TN;   // transfers per wave and chunk
+    constexpr int IPC = IA + IB;
+    constexpr int ROWS_I = VEC == 4 ? 16 : 4;     // rows that one transfer fills
+    constexpr int BUF = (BM + BN) * KC;           // words of one buffer: A's rows, then B's
+    constexpr int NST = TM * TN * 4;              // 16-byte stores of a wave's tile
+    constexpr int AHEAD = NBUF - 1;               // chunks requested ahead
+    constexpr int YOUNGER = (AHEAD - 2) * IPC;    // transfers younger than the chunk that is waited for
+    static_assert(IPC <= 32, "the wait counter holds at most 63 transfers");
+    extern __shared__ __align__(16) uint32_t smem[];
 
     const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, half = lane >> 5;
+    // this wave's scratch of the epilogue: thresholds of its channels, or 32 x 32 sums
+    float *Tw = reinterpret_cast<float *>(smem + NBUF * BUF) + wave * XW;
+    int32_t *Xw = reinterpret_cast<int32_t *>(Tw);
 
-    const int nblk = (int)gridDim.x;
-    int tile = (int)blockIdx.x;
-    if ((nblk & 7) == 0) tile = (int)(blockIdx.x & 7) * (nblk >> 3) + (int)(blockIdx.x >> 3);
-    int64_t m0, n0;
-    {
-        const int band = tile / (8 * gw.nbn);
+    // ---- this block's tiles: numbers first, first + stride, ... of its XCD's share
+    const int xcd = (int)blockIdx.x & 7, stride = (int)gridDim.x >> 3;
+    const int x0 = (int)((int64_t)gw.tiles * xcd >> 3), x1 = (int)((int64_t)gw.tiles * (xcd + 1) >> 3);
+    int tile = x0 + ((int)blockIdx.x >> 3);
+    if (tile >= x1) return;
+    auto origin = [&](int tl, int64_t &m0, int64_t &n0) {
+        const int band = tl / (8 * gw.nbn);
         const int rows_in_band = min(8, gw.nbm - band * 8);
-        const int idx = tile - band * 8 * gw.nbn;
+        const int idx = tl - band * 8 * gw.nbn;
         const int nb = idx / rows_in_band;
         m0 = (int64_t)(band * 8 + (idx - nb * rows_in_band)) * BM;
         n0 = (int64_t)nb * BN;
-    }
+    };
 
-    // staging: a chunk of a tile is (rows x UPR) 16-byte units; SA units of A, SB of B per thread
-    uint4 pa[SA], pb[SB];
-    auto prefetch = [&](int k0) {
-#pragma unroll
-        for (int r = 0; r < SA; ++r) {
-            const int idx = t + 256 * r;
-            pa[r] = load_row_words<VEC>(A, m0 + idx / UPR, M, Kw, k0 + (idx % UPR) * 4);
-        }
-#pragma unroll
-        for (int r = 0; r < SB; ++r) {
-            const int idx = t + 256 * r;
-            pb[r] = load_row_words<VEC>(B, n0 + idx / UPR, N, Kw, k0 + (idx % UPR) * 4);
+    // ---- transfers.  Transfer j of this wave fills rows ROWS_I * (wave + 4 j) .. of A's (B's) part.
+    const int nchunks = (Kw + KC - 1) / KC;
+    const unsigned row_bytes = (unsigned)Kw * 4u;
+    const int f_row = ROWS_I * wave + (VEC == 4 ? lane >> 2 : lane >> 4);
+    const int f_unit = (VEC == 4 ? lane & 3 : (lane >> 2) & 3) ^ ((f_row >> 1) & 3);    // the same for every j
+    const int f_word = f_unit * 4 + (VEC == 4 ? 0 : lane & 3);
+    const unsigned f_off = (unsigned)f_row * row_bytes + (unsigned)f_word * 4u;
+    const unsigned f_step = (unsigned)(4 * ROWS_I) * row_bytes;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) uint32_t *)smem +
+                          (unsigned)wave * (ROWS_I * KC * 4);
+    int tile_f = tile, c_f = 0, buf_f = 0;        // the chunk that is requested next, and its buffer
+    v4i ra, rb;
+    auto set_fetch_tile = [&]() {
+        int64_t m0 = 0, n0 = 0;
+        const bool on = tile_f < x1;
+        if (on) origin(tile_f, m0, n0);
+        // (past the block's last tile: an empty resource, every transfer delivers zeros, so that the
+        // number of transfers in flight never depends on the tile)
+        ra = make_raw_rsrc(A + m0 * Kw, on ? (unsigned)(M - m0 < BM ? M - m0 : BM) * row_bytes : 0u);
+        rb = make_raw_rsrc(B + n0 * Kw, on ? (unsigned)(N - n0 < BN ? N - n0 : BN) * row_bytes : 0u);
+    };
+    // transfer j of the chunk (tile_f, c_f): A's first, then B's.  A word past K must not read the
+    // next row: it addresses past the end of the resource instead.
+    auto fetch = [&](int j) {
+        const unsigned base = c_f * KC + f_word < Kw ? f_off + (unsigned)c_f * (KC * 4) : 0x80000000u;
+        const bool is_a = j < IA;
+        const int jj = is_a ? j : j - IA;
+        const unsigned voff = base + (unsigned)jj * f_step;
+        const unsigned at = lds0 + (unsigned)buf_f * (BUF * 4) + (unsigned)((is_a ? 0 : BM) + 4 * ROWS_I * jj) * (KC * 4);
+        if (VEC == 4) lds_dma16(is_a ? ra : rb, at, voff);
+        else lds_dma4(is_a ? ra : rb, at, voff);
+    };
+    auto fetch_next = [&]() {
+        buf_f = buf_f + 1 == NBUF ? 0 : buf_f + 1;
+        if (++c_f == nchunks) {
+            c_f = 0;
+            tile_f += stride;
+            set_fetch_tile();
         }
     };
-    prefetch(0);
-
-    // Several rounds of 256 x 256 tiles (one block per compute unit at a time): the first round's
-    // blocks start spread over a few microseconds.  Every later block starts when a compute unit
-    // falls free, so tiles keep ending at different times on different compute units for the whole
-    // run, and the tiles' stores (256 KB each) do not all meet in the memory system at once.
-    // (Bounded wait on the free-running 100 MHz counter.)
-    if (gw.stagger_ticks && blockIdx.x < 256u) {
-        const unsigned long long wait = (unsigned long long)blockIdx.x * gw.stagger_ticks / 256u;
-        const long long t0 = wall_clock64();
-        while ((unsigned long long)(wall_clock64() - t0) < wait) __builtin_amdgcn_s_sleep(16);
+    set_fetch_tile();
+#pragma unroll 1
+    for (int c = 0; c < AHEAD; ++c) {
+#pragma unroll
+        for (int j = 0; j < IPC; ++j) fetch(j);
+        fetch_next();
     }
 
-    // VALU instructions to place behind each MFMA: 7 per expanded word, (TM+TN) words per step
-    constexpr int VPM = (7 * (TM + TN) + TM * TN - 1) / (TM * TN);
     uint32_t sgn = 0x88888888u, one = 0x22222222u;
     asm volatile("" : "+s"(sgn));     // keep both masks in registers (v_and_or_b32 takes no literals)
     asm volatile("" : "+v"(one));
 
-    const int nchunks = (Kw + KC - 1) / KC;
-    const int corr = nchunks * KC * 32 - K;      // padded positions all counted as +1
-    const uint32_t *a_rd = As + (wm * TM * 32 + l32) * LS + half * 4;
-    const uint32_t *b_rd = Bs + (wn * TN * 32 + l32) * LS + half * 4;
+    // a chunk = two groups of 8 words; lane half h owns words [8g + 4h, 8g + 4h + 4) of group g,
+    // i.e. unit 2g + h.  rd[g]: word offset of this lane's unit in a row of the wave's first tile.
+    const int swz = ((l32 >> 1) & 3) ^ half;
+    const int rd[2] = {l32 * KC + swz * 4, l32 * KC + (swz ^ 2) * 4};
+    const int a0 = wm * TM * 32 * KC, b0 = (BM + wn * TN * 32) * KC;
+    uint4 wa[2][TM], wb[2][TN];
+    int buf = 0;                                              // buffer of the current chunk
+    auto load_word = [&](int bf, int g, int w) {              // w: TM tiles of A, then TN of B
+        const uint32_t *p = smem + bf * BUF + rd[g];
+        if (w < TM) wa[g][w] = *reinterpret_cast<const uint4 *>(p + a0 + w * 32 * KC);
+        else wb[g][w - TM] = *reinterpret_cast<const uint4 *>(p + b0 + (w - TM) * 32 * KC);
+    };
+    // transfers complete in order: with at most two younger chunks in flight the first has landed
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((AHEAD - 1) * IPC < 63 ? (AHEAD - 1) * IPC : IPC) : "memory");
 
-    {
+#pragma unroll
+    for (int w = 0; w < TM + TN; ++w) load_word(0, 0, w);
+
+    const int corr = nchunks * KC * 32 - K;      // padded positions all counted as +1
+    int after_stores = 0;                        // 1: the previous tile's epilogue was exactly NST stores
+
+#pragma unroll 1
+    for (; tile < x1; tile += stride) {
+        int64_t m0, n0;
+        origin(tile, m0, n0);
+        // thresholds and flips of this wave's channels, one or two per lane, needed after the sums
+        int thr[(TN + 1) / 2];
+        unsigned flip[(TN + 1) / 2];
+        if (PACKED) {
+#pragma unroll
+            for (int q = 0; q < (TN + 1) / 2; ++q) {
+                const int64_t col = n0 + wn * TN * 32 + q * 64 + lane;
+                const int64_t cl = col < N ? col : N - 1;
+                thr[q] = ep.thr[cl];
+                flip[q] = ep.flip && col < N ? ep.flip[cl] : 0u;
+            }
+        }
+        // (opaque, so that the start value is not kept in registers of its own across the tiles)
+        float start = -(float)corr;
+        asm volatile("" : "+v"(start));
         v16f acc[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = start;
 
-        for (int kc = 0; kc < nchunks; ++kc) {
-            __syncthreads();
+        // operands of the current and the next step (FP4: the low four dwords of an MFMA operand)
+        v4i a[2][TM], b[2][TN];
+        auto operand = [](const v4i &x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; };
+        auto expand4 = [&](uint32_t w) {
+            const v8i e = expand_fp4(w, sgn, one);
+            return v4i{e[0], e[1], e[2], e[3]};
+        };
 #pragma unroll
-            for (int r = 0; r < SA; ++r) {
-                const int idx = t + 256 * r;
-                *reinterpret_cast<uint4 *>(As + (idx / UPR) * LS + (idx % UPR) * 4) = pa[r];
-            }
+        for (int i = 0; i < TM; ++i) a[0][i] = expand4(wa[0][i].x);
 #pragma unroll
-            for (int r = 0; r < SB; ++r) {
-                const int idx = t + 256 * r;
-                *reinterpret_cast<uint4 *>(Bs + (idx / UPR) * LS + (idx % UPR) * 4) = pb[r];
-            }
-            __syncthreads();
-            if (kc + 1 < nchunks) prefetch((kc + 1) * KC);
+        for (int j = 0; j < TN; ++j) b[0][j] = expand4(wb[0][j].x);
 
-            // a chunk = NG groups of 8 words; lane half h owns words [8g + 4h, 8g + 4h + 4).
-            // Operands of step s+1 are expanded on the VALU while the matrix core runs step s.
-            uint4 wa[NG][TM], wb[NG][TN];
+        constexpr int NM = TM * TN, NW = TM + TN;
+#pragma unroll 1
+        for (int c = 0;;) {
+            const int lax = __builtin_amdgcn_readfirstlane(after_stores & (c < AHEAD - 1 ? 1 : 0));
+            const int buf_n = buf + 1 == NBUF ? 0 : buf + 1;
+            // The order below is the issue order (scheduling barriers pin it): each MFMA is followed by
+            // its share of the LDS reads, transfers and next step's operand dwords.
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) wa[g][i] = *reinterpret_cast<const uint4 *>(a_rd + i * 32 * LS + g * 8);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) wb[g][j] = *reinterpret_cast<const uint4 *>(b_rd + j * 32 * LS + g * 8);
-            }
-            v8i a[2][TM], b[2][TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) a[0][i] = expand_fp4(wa[0][i].x, sgn, one);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) b[0][j] = expand_fp4(wb[0][j].x, sgn, one);
-#pragma unroll
-            for (int st = 0; st < NST; ++st) {
+            for (int st = 0; st < 8; ++st) {
                 const int cur = st & 1, nxt = cur ^ 1;
-                if (st + 1 < NST) {
-                    const int g = (st + 1) >> 2, q = (st + 1) & 3;
+                const int g1 = ((st + 1) >> 2) & 1, q1 = (st + 1) & 3;
+                // The next chunk has landed and every wave is past the previous one, whose buffer takes
+                // the chunk after the next two.  One younger chunk may be in flight; in a tile's first
+                // two chunks also the previous tile's stores, which are younger than the chunk waited for.
+                if (st == 4)
+                    asm volatile("s_waitcnt vmcnt(%0)\n\t"
+                                 "s_cmp_lg_u32 %2, 0\n\t"
+                                 "s_cbranch_scc1 .Lgemm_lax%=\n\t"
+                                 "s_waitcnt vmcnt(%1)\n"
+                                 ".Lgemm_lax%=:\n\t"
+                                 "s_barrier" ::"n"(YOUNGER + NST < 63 ? YOUNGER + NST : 63), "n"(YOUNGER), "s"(lax) : "memory", "scc");
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) a[nxt][i] = expand_fp4(word_of(wa[g][i], q), sgn, one);
+                for (int k = 0; k < NM; ++k) {
+                    const int i = k / TN, j = k % TN;
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(b[cur][j]), operand(a[cur][i]),
+                                                                                acc[i][j], 4, 4, 0, 0, 0, 0);
+                    if (st == 0 || st == 4) {
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) b[nxt][j] = expand_fp4(word_of(wb[g][j], q), sgn, one);
-                }
+                        for (int w = k * NW / NM; w < (k + 1) * NW / NM; ++w)
+                            load_word(st == 0 ? buf : buf_n, st == 0 ? 1 : 0, w);
+                    }
+                    if (st == 5) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                        for (int f = k * IPC / NM; f < (k + 1) * IPC / NM; ++f) fetch(f);
+                    }
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            a[cur][i], b[cur][j], acc[i][j], 4, 4, 0, 0, 0, 0);
-                // interleave: one MFMA, then its share of the next step's VALU work
-#pragma unroll
-                for (int k = 0; k < TM * TN; ++k) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
+                    for (int d = k * 4 * NW / NM; d < (k + 1) * 4 * NW / NM; ++d) {
+                        const int w = d >> 2, part = d & 3;
+                        if (w < TM) a[nxt][w][part] = (int)expand_part(word_of(wa[g1][w], q1), part, sgn, one);
+                        else b[nxt][w - TM][part] = (int)expand_part(word_of(wb[g1][w - TM], q1), part, sgn, one);
+                        // (used here, lest the next chunk's first operands be made after the last MFMA)
+                        if (st == 7 && part == 3) asm volatile("" ::"v"(w < TM ? a[nxt][w] : b[nxt][w - TM]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            buf = buf_n;
+            fetch_next();
+            if (++c == nchunks) break;
         }
 
-        // ---- epilogue.  Accumulator register r of lane (l32, half) in tile (i, j) is
-        // row 32i + 8(r/4) + 4*half + r%4, column 32j + l32.
-        const int64_t rbase = m0 + wm * TM * 32 + half * 4;
-        const int64_t cbase = n0 + wn * TN * 32 + l32;
-        if (ep.preact) {
-            if (TM * TN >= 16 && m0 + BM <= M && n0 + BN <= N && (int64_t)(BM - 1) * N + BN <= 0x1fffffffLL) {
-                // A whole tile inside C: the stores go through a buffer resource over the tile's
-                // part of C, so that a store is one conversion and one instruction -- the lane's part
-                // of the address is fixed, the row of a register is a scalar offset, the column tile
-                // an immediate.  Streaming stores: C is not read again by this kernel.
-                const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
-                    ep.preact + (m0 * N + n0), 0, (int)(((int64_t)(BM - 1) * N + BN) * 4), 0x00020000);
-                const unsigned row_bytes = (unsigned)N * 4u;
-                const unsigned c_voff = (unsigned)(((wm * TM * 32 + half * 4) * (unsigned)N + wn * TN * 32 + l32) * 4u);
+        // ---- epilogue: register r of lane (l32, half) in tile (i, j) is row 32i + l32 of the wave's part,
+        // column 32j + 8(r/4) + 4*half + r%4
+        const int row0 = wm * TM * 32 + l32, col0 = wn * TN * 32;
+        const int rows = (int)(M - m0 < BM ? M - m0 : BM);
+        after_stores = 0;
+        if constexpr (RAW) {
+            // One 32 x 32 tile after the other through the wave's own LDS area, so that a store covers
+            // eight rows of 128 contiguous bytes: a lane writes its row's four quads of columns (quad c of
+            // row r at position c ^ (r % 8): no bank conflicts either way) and reads quad lane % 8 of
+            // rows lane / 8 + 8k.  Whole cache lines matter: quads stored as they come out of the
+            // accumulators (32 bytes to a row) take 308 us at 8192^3, 64 bytes to a row 212 us, this
+            // 195 us.  The stores go through a buffer resource over the tile's rows of C (the launcher
+            // sees to it that 32-bit offsets reach them): a row past M or a column past N addresses past
+            // its end and is dropped.
+            const unsigned c_row = (unsigned)N * 4u;
+            const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
+                ep.preact + m0 * N, 0, (int)((unsigned)rows * c_row), 0x00020000);
+            const int sr = lane >> 3, sq = lane & 7;
+            int32_t *wr[4];
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const unsigned soff = (unsigned)(i * 32 + (r >> 2) * 8 + (r & 3)) * row_bytes;
-#pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            __builtin_amdgcn_raw_buffer_store_b32((int)acc[i][j][r] - corr, crs, c_voff + j * 128, soff,
-                                                                  2 /* nontemporal */);
-                    }
-            } else {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int64_t col = cbase + j * 32;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int64_t row = rbase + i * 32 + (r >> 2) * 8 + (r & 3);
-                            if (row < M && col < N) ep.preact[row * N + col] = (int)acc[i][j][r] - corr;
-                        }
-                    }
-            }
-        }
-        if (ep.packed) {
-            // A ballot over the 32 columns of a tile is the packed word of one row (one per lane
-            // half).  Lane r of each half keeps the word of register r, so that a tile's 32 words
-            // leave with one store instruction per row block instead of one per word.
-            const int64_t nw = (N + 31) >> 5;
-            int thr[TN];
-            bool flip[TN], cok[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = cbase + j * 32;
-                cok[j] = col < N;
-                thr[j] = cok[j] ? ep.thr[col] : 0;
-                flip[j] = cok[j] && ep.flip && ep.flip[col];
-            }
-            const int64_t wi0 = (n0 + wn * TN * 32) >> 5;
+            for (int q = 0; q < 4; ++q) wr[q] = Xw + l32 * 32 + (((2 * q + half) ^ (l32 & 7)) << 2);
+            const int32_t *rp = Xw + sr * 32 + ((sq ^ sr) << 2);
+            const unsigned col = (unsigned)(n0 + col0) + sq * 4u;            // of tile column 0
+            unsigned at = (unsigned)(wm * TM * 32 + sr) * c_row + col * 4u;
+            const bool whole = (N & 3) == 0 || n0 + BN <= N;                // a quad is all inside or all outside
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                unsigned mine[TN];
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    mine[j] = 0;
+                    if (!PACKED) pin_acc(acc[i][j]);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int x = (int)acc[i][j][r] - corr;
-                        const bool bit = cok[j] && ((x > thr[j]) != flip[j]);
-                        const unsigned long long mask = __ballot(bit);
-                        const unsigned word = half ? (unsigned)(mask >> 32) : (unsigned)mask;
-                        if (l32 == r) mine[j] = word;
-                    }
-                }
-                const int64_t row = rbase + i * 32 + (l32 >> 2) * 8 + (l32 & 3);
-                if (l32 < 16 && row < M) {
-                    uint32_t *dst = ep.packed + row * nw + wi0;
-                    if (TN == 2 && (nw & 1) == 0 && wi0 + 1 < nw) {
-                        *reinterpret_cast<uint2 *>(dst) = make_uint2(mine[0], mine[TN - 1]);
-                    } else if (TN == 4 && (nw & 3) == 0 && wi0 + 3 < nw) {
-                        *reinterpret_cast<uint4 *>(dst) = make_uint4(mine[0], mine[1 % TN], mine[2 % TN], mine[3 % TN]);
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<int4 *>(wr[q]) = make_int4((int)acc[i][j][q * 4], (int)acc[i][j][q * 4 + 1],
+                                                                     (int)acc[i][j][q * 4 + 2], (int)acc[i][j][q * 4 + 3]);
+                    // (other lanes of the wave read what this one wrote: LDS keeps a wave's order)
+                    asm volatile("" ::: "memory");
+                    v4i x[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) x[k] = *reinterpret_cast<const v4i *>(rp + k * 256);
+                    asm volatile("" ::: "memory");
+                    if (whole) {
+                        const unsigned aj = col + j * 32 < (unsigned)N ? at + j * 128 : 0x80000000u;
+                        // streaming stores, unless a row's 128 bytes lie in two cache lines (6000 x 6001, K = 4096:
+                        // 147 us with streaming stores, 81 us without)
+                        if ((N & 31) == 0) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                __builtin_amdgcn_raw_buffer_store_b128(x[k], crs, aj + k * 8 * c_row, 0, 2);
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                __builtin_amdgcn_raw_buffer_store_b128(x[k], crs, aj + k * 8 * c_row, 0, 0);
+                        }
                     } else {
 #pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            if (wi0 + j < nw) dst[j] = mine[j];
+                        for (int e = 0; e < 4; ++e) {
+                            const unsigned ae = col + j * 32 + e < (unsigned)N ? at + (j * 128 + e * 4) : 0x80000000u;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k)
+                                __builtin_amdgcn_raw_buffer_store_b32(x[k][e], crs, ae + k * 8 * c_row, 0, 0);
+                        }
                     }
+                    __builtin_amdgcn_sched_barrier(0);      // one tile's registers at a time
+                }
+                at += 32 * c_row;
+            }
+            after_stores = whole && !PACKED;
+        }
+        if constexpr (PACKED) {
+            // thresholds through LDS (written and read by the same wave) into the accumulators' channel
+            // order; T - x is negative iff x > T (both exact, a difference never rounds to zero)
+            unsigned flipw[TN];
+#pragma unroll
+            for (int q = 0; q < (TN + 1) / 2; ++q) {
+                const int bound = K + 1;                      // no sum reaches it
+                const int th = thr[q] > bound ? bound : (thr[q] < -bound ? -bound : thr[q]);
+                if (q * 64 + lane < TN * 32) Tw[q * 64 + lane] = (float)th;
+                const unsigned long long fl = __ballot(flip[q] != 0);
+                flipw[2 * q] = (unsigned)fl;
+                if (2 * q + 1 < TN) flipw[2 * q + 1] = (unsigned)(fl >> 32);
+            }
+            asm volatile("" ::: "memory");
+            const int64_t nw = (N + 31) >> 5, w0 = (n0 + col0) >> 5;
+            auto okw = [&](int j) {                           // channels of tile j that exist
+                const int64_t left = N - (n0 + col0 + j * 32);
+                return left >= 32 ? 0xffffffffu : (left <= 0 ? 0u : (1u << left) - 1u);
+            };
+            constexpr int JS = TN % 2 == 0 ? 2 : 1;
+#pragma unroll
+            for (int jp = 0; jp < TN; jp += JS) {
+                v16f tv[JS];
+#pragma unroll
+                for (int u = 0; u < JS; ++u) tv[u] = load_bias16<v16f>(Tw + (jp + u) * 32, half);
+                unsigned fl = flipw[jp], ok = okw(jp);
+                if (JS == 2) {
+                    fl = half ? flipw[jp + JS - 1] : fl;
+                    ok = half ? okw(jp + JS - 1) : ok;
+                }
+                const int64_t wi = w0 + jp + (JS == 2 ? half : 0);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    if (!RAW) pin_acc(acc[i][jp]);
+                    if (!RAW && JS == 2) pin_acc(acc[i][jp + JS - 1]);
+                    const unsigned lo = tile_half_word<false>([&](int r) { return tv[0][r] - acc[i][jp][r]; });
+                    const unsigned hi =
+                        JS == 2 ? tile_half_word<false>([&](int r) { return tv[JS - 1][r] - acc[i][jp + JS - 1][r]; }) : lo;
+                    // two tiles' words: the first complete in lanes 0..31, the second in lanes 32..63
+                    const auto sw = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+                    const unsigned word = (merge_half_words(sw[0], sw[1]) ^ fl) & ok;
+                    if (row0 + i * 32 < rows && wi < nw && (JS == 2 || half == 0))
+                        ep.packed[(m0 + row0 + i * 32) * nw + wi] = word;
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
     }
+    // nothing may be on its way to LDS when the block gives it back
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Small dense problems (the 64 x 64 tiling would leave most compute units idle): a block owns
@@ -582,25 +679,52 @@ __global__ __launch_bounds__(512) void bgemv_rows(const uint32_t *__restrict__ A
     }
 }
 
+template <int TM, int TN, int VEC, bool RAW, bool PACKED>
+bnn_status launch_mfma_out(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n, int kw,
+                           const GemmWalk &gw, const EpiArgs &ep, hipStream_t s)
+{
+    // blocks per compute unit: the 256 x 256 tile fills the registers, the smaller ones the LDS
+    constexpr int OCC = TM * TN >= 16 ? 1 : 2;
+    constexpr int RES = TM * TN >= 16 ? 1 : (TM * TN >= 4 ? 2 : 3);
+    constexpr unsigned smem = (NBUF * 64 * (TM + TN) * KC + 4 * XW) * 4;
+    static_assert(RES * smem <= 160 * 1024, "LDS of the resident blocks");
+    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel
+        static std::once_flag once;
+        static hipError_t raise_err = hipSuccess;
+        std::call_once(once, [] {
+            raise_err = hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED>,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        });
+        if (raise_err != hipSuccess) return hip_result(raise_err);
+    }
+    // a whole number of blocks per XCD; those without a tile leave at once
+    const unsigned blocks = 8u * (unsigned)ceil_div64(gw.tiles < 256 * RES ? gw.tiles : 256 * RES, 8);
+    hipLaunchKernelGGL((bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED>), dim3(blocks), dim3(256), smem, s, a, b, m, n, kw,
+                       (int)k, gw, ep);
+    return hip_result(hipGetLastError());
+}
+
+template <int TM, int TN, int VEC>
+bnn_status launch_mfma_vec(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n, int kw,
+                           const GemmWalk &gw, const EpiArgs &ep, hipStream_t s)
+{
+    if (!ep.packed) return launch_mfma_out<TM, TN, VEC, true, false>(a, m, k, b, n, kw, gw, ep, s);
+    if (!ep.preact) return launch_mfma_out<TM, TN, VEC, false, true>(a, m, k, b, n, kw, gw, ep, s);
+    if constexpr (TM * TN < 16) return launch_mfma_out<TM, TN, VEC, true, true>(a, m, k, b, n, kw, gw, ep, s);
+    else return BNN_ERR_UNSUPPORTED;
+}
+
 template <int TM, int TN>
 bnn_status launch_mfma(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n, int kw,
                        const EpiArgs &ep, hipStream_t s)
 {
     GemmWalk gw;
     const int64_t nbm = ceil_div64(m, 64 * TM), nbn = ceil_div64(n, 64 * TN);
-    const int64_t blocks = nbm * nbn;
-    if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
-    gw.nbm = (int)nbm; gw.nbn = (int)nbn;
-    // two or more rounds of the 256 x 256 tile: the first round starts spread over 10 us
-    gw.stagger_ticks = (TM * TN >= 16 && blocks >= 512) ? 1000 : 0;
-    dim3 grid((unsigned)blocks);
-    if ((kw & 3) == 0)
-        hipLaunchKernelGGL((bgemm_mfma<TM, TN, 4>), grid, dim3(256), 0, s, a, b, m, n, kw, (int)k, gw, ep);
-    else if ((kw & 1) == 0)
-        hipLaunchKernelGGL((bgemm_mfma<TM, TN, 2>), grid, dim3(256), 0, s, a, b, m, n, kw, (int)k, gw, ep);
-    else
-        hipLaunchKernelGGL((bgemm_mfma<TM, TN, 1>), grid, dim3(256), 0, s, a, b, m, n, kw, (int)k, gw, ep);
-    return hip_result(hipGetLastError());
+    const int64_t tiles = nbm * nbn;
+    if (tiles > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
+    gw.nbm = (int)nbm; gw.nbn = (int)nbn; gw.tiles = (int)tiles;
+    if ((kw & 3) == 0) return launch_mfma_vec<TM, TN, 4>(a, m, k, b, n, kw, gw, ep, s);
+    return launch_mfma_vec<TM, TN, 1>(a, m, k, b, n, kw, gw, ep, s);
 }
 
 // more than 8 rows, too few tiles for any of the three block tiles
@@ -614,7 +738,9 @@ bnn_status launch_small(const uint32_t *a, int64_t m, int64_t k, const uint32_t 
                         const EpiArgs &ep, const FcTailArgs &tail, hipStream_t s)
 {
     const int nbn = (int)ceil_div64(n, 32);
-    const dim3 grid((unsigned)(nbn * ceil_div64(m, 32)));
+    const int64_t blocks = nbn * ceil_div64(m, 32);
+    if (blocks > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)blocks);
     if ((kw & 3) == 0)
         hipLaunchKernelGGL((bgemm_small<4, TAIL>), grid, dim3(256), 0, s, a, b, m, n, kw, (int)k, nbn, ep, tail);
     else if ((kw & 1) == 0)
@@ -658,12 +784,17 @@ bnn_status launch_fc_binary(const uint32_t *a, int64_t m, int64_t k, const uint3
         const FcTailArgs none = {nullptr, nullptr, 0};
         return launch_gemv<false>(a, m, k, b, n, kw, ep, none, s);
     }
-    // largest tile that still fills most of the 256 compute units
+    // largest tile that still fills most of the 256 compute units (and whose rows of raw output a
+    // 32-bit offset reaches: the kernels' stores go through a buffer resource over them)
     const int64_t want = 192;
-    if (ceil_div64(m, 256) * ceil_div64(n, 256) >= want) return launch_mfma<4, 4>(a, m, k, b, n, kw, ep, s);
-    if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want) return launch_mfma<2, 2>(a, m, k, b, n, kw, ep, s);
+    auto reach = [&](int rows) { return !ep.preact || rows * n < (int64_t)1 << 29; };
+    const bool both = ep.preact && ep.packed;       // diagnostic calls: the 256 x 256 tile would spill
+    if (!both && ceil_div64(m, 256) * ceil_div64(n, 256) >= want && reach(256))
+        return launch_mfma<4, 4>(a, m, k, b, n, kw, ep, s);
+    if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want && reach(128))
+        return launch_mfma<2, 2>(a, m, k, b, n, kw, ep, s);
     // fewer than that many 64 x 64 tiles: 32 x 32 tiles with K split over the block's waves
-    if (fc_takes_small_kernel(m, n)) {
+    if (fc_takes_small_kernel(m, n) || !reach(64)) {
         const FcTailArgs none = {nullptr, nullptr, 0};
         return launch_small<false>(a, m, k, b, n, kw, ep, none, s);
     }

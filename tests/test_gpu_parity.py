@@ -112,6 +112,37 @@ def test_fc_binary_raw_and_fused(m, n, k):
     np.testing.assert_array_equal(host_u32(packed2), pack_pm1(oracle.step(want, thr, None)))
 
 
+# The persistent tile kernels at their edges: several tiles per block, one to three K chunks of 512
+# bits, rows that are and are not whole 16-byte units, columns that end inside a quad, inside a
+# cache line, and on one; first the 256 x 256 tile, then 128 x 128, then 64 x 64.
+@pytest.mark.parametrize("m,n,k", [(4352, 4352, 512), (4097, 4352, 1024), (4200, 4401, 520), (4100, 4500, 1500),
+                                   (2560, 4864, 256), (2500, 4801, 1100), (2561, 4610, 33), (900, 1000, 200),
+                                   (777, 1029, 1537)])
+def test_fc_binary_tile_rounds(m, n, k):
+    print("fc rounds", m, n, k, flush=True)
+    rng = rng_of(m + 2 * n + 3 * k)
+    a, b = pm1(rng, (m, k)), pm1(rng, (n, k))
+    want = oracle.fc(a, b)
+    ad, bd = dev(pack_pm1(a)), dev(pack_pm1(b))
+    c = fill_i32((m + 1, n), 123456)                     # one row behind the result stays untouched
+    P.bnn_fc_binary(ad, m, k, bd, n, c_out=c)
+    np.testing.assert_array_equal(c[:m].cpu().numpy(), want)
+    assert int((c[m] != 123456).sum()) == 0
+    thr = want[m // 2].copy()                            # ties
+    thr[::3] = rng.integers(-(k // 4) - 1, k // 4 + 2, size=thr[::3].size)
+    thr[-2:] = [np.iinfo(np.int32).max, np.iinfo(np.int32).min]
+    flip = rng.integers(0, 2, size=n).astype(np.uint8)
+    bits = pack_pm1(oracle.step(want, thr, flip))
+    packed = fill_i32((m + 1, (n + 31) // 32), -1)
+    P.bnn_fc_binary(ad, m, k, bd, n, thr=dev(thr), flip=dev(flip), packed_out=packed)
+    np.testing.assert_array_equal(host_u32(packed[:m]), bits)
+    assert int((packed[m] != -1).sum()) == 0
+    c2, packed2 = fill_i32((m, n), 5), fill_i32((m, (n + 31) // 32), -1)
+    P.bnn_fc_binary(ad, m, k, bd, n, thr=dev(thr), flip=dev(flip), c_out=c2, packed_out=packed2)
+    np.testing.assert_array_equal(c2.cpu().numpy(), want)
+    np.testing.assert_array_equal(host_u32(packed2), bits)
+
+
 def test_fc_binary_with_gpu_packed_operands_and_empty_batch():
     rng = rng_of(77)
     a, b = pm1(rng, (70, 777)), pm1(rng, (90, 777))
