@@ -81,7 +81,7 @@ constexpr bool weights_resident(int tm, int tn, int wph)
 }
 
 struct TileCoord {
-    int group, ty, tx;           // image group, tile row, tile column
+    int group, ty, tx;           // image group, tile row, tile column (LIN: first image, first unit inside it, -)
 };
 
 struct ConvGeom {
@@ -97,6 +97,11 @@ struct ConvGeom {
     unsigned mg_pw, mg_ph;       // ceil(2^32 / d) for d = patch width, patch height (staging index math)
     int step_group, step_ty, step_tx;    // `slots` pixel tiles as an (image group, tile row, tile column) increment
     unsigned mg_co, mg_tpg, mg_tx;       // magic_floor of n_co_tiles, tiles per image group, tiles_x
+    // linear tiles (LIN)
+    int win;                     // 1: a unit is a 2x2 window, 0: a pixel
+    int upi, ww;                 // units per image, per row of units
+    int step_img, step_u;        // `slots` tiles as an (image, unit) increment
+    unsigned mg_upi, mg_ww, mg_hp;       // magic_floor of upi, ww, h + 2
 };
 
 // WPH = words per lane half per tap; the layer's cw words per pixel are zero-padded to 2*WPH.
@@ -115,7 +120,16 @@ struct ConvGeom {
 // behind the current one and a chunk costs one barrier.  Rows are unpadded (16 words) and
 // their 8-byte units are stored at position unit ^ ((row >> 1) & 7), which keeps the 32 rows
 // read by one instruction on distinct banks.
-template <int TM, int TN, int WPH, bool WDMA = false>
+//
+// LIN: a tile is the next 64*TM pixels (2x2 windows when pooling) of the batch in raster order
+// instead of a rectangle per image group, so that images of any size fill their tiles: 21 x 21
+// images take 441 rows of the implicit GEMM each, 1024 with 16 x 16 rectangles.  The patch is then
+// the padded rows (w + 2 pixels; an image has h + 2 of them) that these pixels touch, a pixel's place
+// in it is worked out per tile, and the output words are contiguous.  Rectangles stay where the
+// image is made of them exactly (no work per tile for the addresses) and where whole rows do not
+// fit LDS.  Rectangles / linear tiles, us: 200 x 17 x 17, 224 -> 224 48.0 / 18.5; 105 x 21 x 21, 128 -> 320
+// 18.1 / 13.9; 1137 x 7 x 7, 320 -> 184 53.5 / 39.8; 131 x 27 x 31, 256 -> 64 19.2 / 14.7.
+template <int TM, int TN, int WPH, bool WDMA, bool LIN>
 __global__ __launch_bounds__(256, 2)
 void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt, ConvGeom g, EpiArgs ep)
 {
@@ -155,8 +169,11 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     const int co_tile = bid - slot * g.n_co_tiles;
     const int th = 1 << g.lth, tw = 1 << g.ltw;
     const int o_blk = co_tile * BN;
-    const int pw = tw + 2, ph = th + 2;
+    const int pw = LIN ? g.w + 2 : tw + 2, ph = LIN ? g.h + 2 : th + 2;
     const int tiles_per_group = g.tiles_x * g.tiles_y;
+    const int UB = LIN ? (g.win ? 16 * TM : 64 * TM) : 0;            // units per tile
+    // image row of a unit (first row of a window), relative to its image
+    auto unit_row = [&](int rem) { return div_by(rem, g.ww, g.mg_ww) << g.win; };
 
     // ---- per-channel step parameters and (if resident) all weight chunks: once per block,
     // requested further down, behind the first patch, so that all of it is in flight together
@@ -269,22 +286,30 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     // the layer has exactly CWP words per pixel and CWP >= 4, else one word.
     const bool wide = (g.cw == CWP) && (CWP >= 4);
     auto fetch_patch = [&](const TileCoord &tc, int buf) {
-        const int img0 = tc.group * g.ni;
-        const int y0 = tc.ty * th, x0 = tc.tx * tw;
-        const int imgs = min(g.ni, g.n - img0);
+        const int img0 = LIN ? tc.group : tc.group * g.ni;
+        const int y0 = LIN ? unit_row(tc.ty) : tc.ty * th, x0 = LIN ? 0 : tc.tx * tw;
+        int imgs = g.n - img0, rows = 0;
+        if (LIN) {                      // padded rows from above the first pixel's to below the last one's
+            const int il = div_by(tc.ty + UB - 1, g.upi, g.mg_upi);
+            rows = il * ph + unit_row(tc.ty + UB - 1 - il * g.upi) + g.win + 3 - y0;
+            imgs = min(il + 1, imgs);
+        } else {
+            imgs = min(g.ni, imgs);
+        }
         const uint32_t *base = in + (int64_t)img0 * g.h * g.w * g.cw;
         const unsigned bytes = (unsigned)imgs * g.h * g.w * g.cw * 4;
         const v4i rsrc = make_raw_rsrc(base, bytes);
         // LDS byte address of the destination buffer
         const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) uint32_t *)(Ps + buf * g.patch_words);
         const int upp = wide ? CWP / 4 : CWP;               // units per pixel
-        const int total = g.ni * ph * pw * upp;
+        const int total = (LIN ? rows : g.ni * ph) * pw * upp;
         for (int b0 = 0; b0 < total; b0 += 256) {
             const int idx = b0 + t;
             // idx -> (image, row, column, unit) of the patch; divisions by multiply-high
             const int p0 = idx / upp, u = idx - p0 * upp;
             const int p1 = (int)__umulhi((unsigned)p0, g.mg_pw), px = p0 - p1 * pw;
-            const int il = (int)__umulhi((unsigned)p1, g.mg_ph), py = p1 - il * ph;
+            const int il = LIN ? div_by(y0 + p1, ph, g.mg_hp) : (int)__umulhi((unsigned)p1, g.mg_ph);
+            const int py = p1 - il * ph;
             const int y = y0 + py - 1, x = x0 + px - 1;
             const bool inside = y >= 0 && y < g.h && x >= 0 && x < g.w && (wide || u < g.cw);
             unsigned voff = 0x80000000u;                    // past the end of the buffer: zeros
@@ -299,15 +324,30 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
 
     // ---- this lane's pixels: implicit-GEMM row p = 4 * window + (2*dy + dx)
     int pixoff[TM];
+    // LIN: of the tile that starts at unit u0 of its first image
+    auto place_pixels = [&](int u0) {
+        const int y0 = unit_row(u0);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int p = wm * TM * 32 + i * 32 + l32;
-        const int wq = p >> 2, sub = p & 3;
-        const int wx = wq & ((tw >> 1) - 1);
-        const int wy = (wq >> (g.ltw - 1)) & ((th >> 1) - 1);
-        const int il = wq >> (g.ltw - 1 + g.lth - 1);
-        const int py = 2 * wy + (sub >> 1), px = 2 * wx + (sub & 1);
-        pixoff[i] = ((il * ph + py) * pw + px) * CWP + half * WPH;
+        for (int i = 0; i < TM; ++i) {
+            const int p = wm * TM * 32 + i * 32 + l32;
+            const int u = u0 + (g.win ? p >> 2 : p);
+            const int il = div_by(u, g.upi, g.mg_upi), rem = u - il * g.upi;
+            const int ry = div_by(rem, g.ww, g.mg_ww), rx = rem - ry * g.ww;
+            const int y = g.win ? 2 * ry + ((p >> 1) & 1) : ry, x = g.win ? 2 * rx + (p & 1) : rx;
+            pixoff[i] = ((il * ph + y - y0) * pw + x) * CWP + half * WPH;
+        }
+    };
+    if (!LIN) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int p = wm * TM * 32 + i * 32 + l32;
+            const int wq = p >> 2, sub = p & 3;
+            const int wx = wq & ((tw >> 1) - 1);
+            const int wy = (wq >> (g.ltw - 1)) & ((th >> 1) - 1);
+            const int il = wq >> (g.ltw - 1 + g.lth - 1);
+            const int py = 2 * wy + (sub >> 1), px = 2 * wx + (sub & 1);
+            pixoff[i] = ((il * ph + py) * pw + px) * CWP + half * WPH;
+        }
     }
     const int browoff = (wn * TN * 32 + l32) * LSB + half * SPC;
 
@@ -320,11 +360,23 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     // `slots` tiles is a fixed (group, y, x) increment with carries
     TileCoord step, prev, cur, next;
     step.group = g.step_group; step.ty = g.step_ty; step.tx = g.step_tx;
-    next.group = div_by(slot, tiles_per_group, g.mg_tpg);
-    next.ty = div_by(slot - next.group * tiles_per_group, g.tiles_x, g.mg_tx);
-    next.tx = slot - next.group * tiles_per_group - next.ty * g.tiles_x;
+    if (LIN) {
+        next.group = div_by(slot * UB, g.upi, g.mg_upi);
+        next.ty = slot * UB - next.group * g.upi;
+        next.tx = 0;
+    } else {
+        next.group = div_by(slot, tiles_per_group, g.mg_tpg);
+        next.ty = div_by(slot - next.group * tiles_per_group, g.tiles_x, g.mg_tx);
+        next.tx = slot - next.group * tiles_per_group - next.ty * g.tiles_x;
+    }
     prev = cur = next;
     auto advance = [&](TileCoord &c) {
+        if (LIN) {
+            c.ty += g.step_u;
+            c.group += g.step_img;
+            if (c.ty >= g.upi) { c.ty -= g.upi; ++c.group; }
+            return;
+        }
         c.tx += step.tx;
         if (c.tx >= g.tiles_x) { c.tx -= g.tiles_x; ++c.ty; }
         c.ty += step.ty;
@@ -338,7 +390,20 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
         return pos;
     };
 
-    const CopyLane copy_lane = make_copy_lane(64 * TM, tile_pos(next), ep.pool, t);
+    CopyLane copy_lane;
+    if (!LIN) copy_lane = make_copy_lane(64 * TM, tile_pos(next), ep.pool, t);
+    // packed words of a finished tile, LDS -> global
+    auto copy_out = [&](const uint32_t *tile, const TileCoord &c) {
+        if (!LIN) {
+            conv_tile_copy_out<BW>(tile, copy_lane, o_blk >> 5, tile_pos(c), ep);
+        } else {
+            const int cwo = (g.c_out + 31) >> 5;
+            const int64_t left = (int64_t)(g.n - c.group) * g.upi - c.ty;      // units from the tile's first
+            if (t < UB && t < left)
+                copy_words<BW>(tile + t * BW, ep.packed + ((int64_t)c.group * g.upi + c.ty + t) * cwo + (o_blk >> 5),
+                               cwo, o_blk >> 5);
+        }
+    };
     if (slot < g.n_ptiles) fetch_patch(next, 0);
     if (WDMA && slot < g.n_ptiles) dma_w(0, 0);
     // resident weights (at most 48 registers per thread), flips and thresholds: every load is
@@ -373,7 +438,8 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
         __syncthreads();                                      // ... for every wave; previous tile fully consumed
         if (g.dbuf && ptile + g.slots < g.n_ptiles) fetch_patch(next, buf ^ 1);
         if (ep.packed && it > 0)
-            conv_tile_copy_out<BW>(Os + ((it - 1) & 1) * (64 * TM * BW), copy_lane, o_blk >> 5, tile_pos(prev), ep);
+            copy_out(Os + ((it - 1) & 1) * (64 * TM * BW), prev);
+        if (LIN) place_pixels(cur.ty);
 
         __builtin_amdgcn_s_setprio(1);                        // the multiply phase outranks another wave's epilogue
         // accumulators start at the channels' biases (see stage_bias_f32)
@@ -538,12 +604,27 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
 
         // ---- epilogue (shared with the first layer)
         __builtin_amdgcn_s_setprio(0);
-        const TilePos pos = tile_pos(cur);
         if (ep.preact) {
             auto getx = [&](int i, int j, int r) {
                 return (int)(acc[i][j][r] - Tw[j * 32 + (r >> 2) * 8 + half * 4 + (r & 3)]) - corr;
             };
-            conv_tile_store_preact<TM, TN>(getx, wm * TM * 32, o_blk + wn * TN * 32, l32, half, pos, ep.preact);
+            if (!LIN) {
+                conv_tile_store_preact<TM, TN>(getx, wm * TM * 32, o_blk + wn * TN * 32, l32, half, tile_pos(cur),
+                                               ep.preact);
+            } else {
+                int row = wm * TM * 32 + l32;
+                asm volatile("" : "+v"(row));             // (see conv_tile_store_preact)
+                auto getpix = [&](int i) -> int64_t {
+                    const int p = row + i * 32;
+                    const int u = cur.ty + (g.win ? p >> 2 : p);
+                    if (u >= (int64_t)(g.n - cur.group) * g.upi) return -1;
+                    if (!g.win) return (int64_t)cur.group * g.upi + u;
+                    const int il = div_by(u, g.upi, g.mg_upi), rem = u - il * g.upi;
+                    const int ry = div_by(rem, g.ww, g.mg_ww), rx = rem - ry * g.ww;
+                    return ((int64_t)(cur.group + il) * g.h + 2 * ry + ((p >> 1) & 1)) * g.w + 2 * rx + (p & 1);
+                };
+                conv_store_preact<TM, TN>(getx, getpix, o_blk + wn * TN * 32, half, g.c_out, ep.preact);
+            }
         }
         if (ep.packed) {
             // bits -> LDS tile [output pixel][2*TN words]; one vector store per pixel later
@@ -558,12 +639,12 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     }
     if (ep.packed && it > 0) {
         __syncthreads();
-        conv_tile_copy_out<BW>(Os + ((it - 1) & 1) * (64 * TM * BW), copy_lane, o_blk >> 5, tile_pos(cur), ep);
+        copy_out(Os + ((it - 1) & 1) * (64 * TM * BW), cur);
     }
 }
 
 template <int TM, int TN, int WPH, bool WDMA>
-bool make_geom(int n, int h, int w, int c_in, int c_out, ConvGeom &g, size_t &smem)
+bool make_geom(int n, int h, int w, int c_in, int c_out, bool win, bool lin, ConvGeom &g, size_t &smem)
 {
     constexpr int V = WPH >= 2 ? 2 : WPH;
     constexpr int LSB = WDMA ? 2 * steps_per_chunk(WPH) : 2 * steps_per_chunk(WPH) + V;
@@ -580,15 +661,36 @@ bool make_geom(int n, int h, int w, int c_in, int c_out, ConvGeom &g, size_t &sm
     g.ltw = ts.ltw; g.lth = ts.lth; g.ni = ts.ni;
     g.tiles_x = ts.tiles_x; g.tiles_y = ts.tiles_y;
     g.n_co_tiles = (c_out + 64 * TN - 1) / (64 * TN);
-    const int64_t ptiles = (int64_t)ts.tiles_x * ts.tiles_y * ((n + ts.ni - 1) / ts.ni);
-    if (ptiles > 0x3fffffffLL || (int64_t)ts.ni * h * w * g.cw * 4 >= 0x7fffffffLL) return false;
+    const int sh = win ? 1 : 0;
+    const int ub = 64 * TM >> (2 * sh);                      // LIN: units per tile
+    int64_t ptiles;
+    int imgs, pwords;                                        // images a patch can touch, its words
+    if (lin) {
+        if (h > 1024 || w > 1024) return false;
+        g.win = sh; g.upi = (h >> sh) * (w >> sh); g.ww = w >> sh;
+        ptiles = ((int64_t)n * g.upi + ub - 1) / ub;
+        // rows of units a tile can touch, rows of pixels, plus two padded rows around them and two more
+        // at every image border inside the tile
+        const int urows = (ub - 1 + g.ww - 1) / g.ww + 1, cross = (ub - 1 + g.upi - 1) / g.upi;
+        imgs = cross + 1;
+        const int64_t pixels = (int64_t)((urows << sh) + 2 + 2 * cross) * (w + 2);
+        if (pixels > 16384) return false;
+        pwords = (int)pixels * (2 * WPH);
+    } else {
+        g.win = 0; g.upi = g.ww = 1;
+        ptiles = (int64_t)ts.tiles_x * ts.tiles_y * ((n + ts.ni - 1) / ts.ni);
+        imgs = ts.ni;
+        pwords = ts.ni * ((1 << ts.lth) + 2) * ((1 << ts.ltw) + 2) * (2 * WPH);
+    }
+    if (ptiles > 0x3fffffffLL || (int64_t)imgs * h * w * g.cw * 4 >= 0x7fffffffLL) return false;
     if (((int64_t)c_out + 64 * TN) * 9 * g.cw >= 0x7fffffffLL) return false;     // 32-bit weight word offsets
     g.n_ptiles = (int)ptiles;
     // exact for dividends below 2^16 (a patch has at most a few thousand units)
-    g.mg_pw = (unsigned)((0x100000000ULL + (1 << ts.ltw) + 1) / ((1 << ts.ltw) + 2));
-    g.mg_ph = (unsigned)((0x100000000ULL + (1 << ts.lth) + 1) / ((1 << ts.lth) + 2));
+    const int pw = lin ? w + 2 : (1 << ts.ltw) + 2, ph = lin ? h + 2 : (1 << ts.lth) + 2;
+    g.mg_pw = (unsigned)((0x100000000ULL + pw - 1) / pw);
+    g.mg_ph = (unsigned)((0x100000000ULL + ph - 1) / ph);
+    g.mg_hp = magic_floor(ph);
     // one patch buffer: pixels x padded words, rounded up to a wave's worth of 16-byte units
-    const int pwords = ts.ni * ((1 << ts.lth) + 2) * ((1 << ts.ltw) + 2) * (2 * WPH);
     g.patch_words = (pwords + 255) & ~255;
     const size_t fixed = (size_t)NBUF * 64 * TN * LSB * 4 + 64 * TN * 4 + (size_t)2 * 64 * TM * 2 * TN * 4;
     g.dbuf = (fixed + 2 * (size_t)g.patch_words * 4 <= (size_t)MAX_SMEM) ? 1 : 0;
@@ -602,10 +704,58 @@ bool make_geom(int n, int h, int w, int c_in, int c_out, ConvGeom &g, size_t &sm
     g.step_group = slots / tpg;
     g.step_ty = (slots - g.step_group * tpg) / ts.tiles_x;
     g.step_tx = slots - g.step_group * tpg - g.step_ty * ts.tiles_x;
+    g.step_img = slots * ub / g.upi;
+    g.step_u = slots * ub - g.step_img * g.upi;
     g.mg_co = magic_floor(g.n_co_tiles);
     g.mg_tpg = magic_floor(tpg);
     g.mg_tx = magic_floor(ts.tiles_x);
+    g.mg_upi = magic_floor(g.upi);
+    g.mg_ww = magic_floor(g.ww);
     return smem <= (size_t)MAX_SMEM;
+}
+
+// Rounds of work of a tiling: how many tiles the busiest block takes; a single round in which no
+// compute unit has two blocks counts for less (they share the matrix pipe otherwise).
+inline double conv_rounds(const ConvGeom &g)
+{
+    if ((int64_t)g.n_ptiles * g.n_co_tiles <= 256) return 0.6;
+    return (g.n_ptiles + g.slots - 1) / g.slots;
+}
+
+// Rectangular or linear tiles, whichever take fewer rounds.  Working out a linear tile's addresses
+// costs some 8 % of a tile (measured where both tilings take the same number of rounds: 28 x 28 images
+// 64 -> 64 at batch 256 11.4 us with rectangles and 12.0 with linear tiles, 449 x 12 x 31 17.0 and 17.8).
+// Returns false if neither fits; *lin says which.
+template <int TM, int TN, int WPH, bool WDMA>
+bool pick_geom(int n, int h, int w, int c_in, int c_out, bool win, ConvGeom &g, size_t &smem, bool *lin)
+{
+    ConvGeom gl;
+    size_t sl;
+    const bool rect_ok = make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, false, g, smem);
+    const bool lin_ok = make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, true, gl, sl);
+    *lin = lin_ok && (!rect_ok || 1.08 * conv_rounds(gl) < conv_rounds(g));
+    if (*lin) { g = gl; smem = sl; }
+    return rect_ok || lin_ok;
+}
+
+template <int TM, int TN, int WPH, bool WDMA, bool LIN>
+bnn_status launch_geom(const uint32_t *in, const uint32_t *wt, const ConvGeom &g, size_t smem, const EpiArgs &ep,
+                       hipStream_t s)
+{
+    const unsigned blocks = (unsigned)(g.slots * g.n_co_tiles);
+    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel
+        // (callers on distinct threads may arrive here together; a failed attempt is reported to
+        // every caller of this kernel, a successful one is never repeated)
+        static std::once_flag once;
+        static hipError_t raise_err = hipSuccess;
+        std::call_once(once, [] {
+            raise_err = hipFuncSetAttribute((const void *)bconv_mfma<TM, TN, WPH, WDMA, LIN>,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, MAX_SMEM);
+        });
+        if (raise_err != hipSuccess) return hip_result(raise_err);
+    }
+    hipLaunchKernelGGL((bconv_mfma<TM, TN, WPH, WDMA, LIN>), dim3(blocks), dim3(256), smem, s, in, wt, g, ep);
+    return hip_result(hipGetLastError());
 }
 
 template <int TM, int TN, int WPH, bool WDMA = false>
@@ -614,32 +764,24 @@ bnn_status launch_one(const uint32_t *in, const uint32_t *wt, int n, int h, int 
 {
     ConvGeom g;
     size_t smem;
-    if (!make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, g, smem)) return BNN_ERR_UNSUPPORTED;
-    const unsigned blocks = (unsigned)(g.slots * g.n_co_tiles);
-    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel
-        // (callers on distinct threads may arrive here together; a failed attempt is reported to
-        // every caller of this kernel, a successful one is never repeated)
-        static std::once_flag once;
-        static hipError_t raise_err = hipSuccess;
-        std::call_once(once, [] {
-            raise_err = hipFuncSetAttribute((const void *)bconv_mfma<TM, TN, WPH, WDMA>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, MAX_SMEM);
-        });
-        if (raise_err != hipSuccess) return hip_result(raise_err);
-    }
-    hipLaunchKernelGGL((bconv_mfma<TM, TN, WPH, WDMA>), dim3(blocks), dim3(256), smem, s, in, wt, g, ep);
-    return hip_result(hipGetLastError());
+    bool lin;
+    if (!pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, ep.packed && ep.pool == 2, g, smem, &lin))
+        return BNN_ERR_UNSUPPORTED;
+    return lin ? launch_geom<TM, TN, WPH, WDMA, true>(in, wt, g, smem, ep, s)
+               : launch_geom<TM, TN, WPH, WDMA, false>(in, wt, g, smem, ep, s);
 }
 
-// Work items (pixel tiles x channel tiles) a (64*TM pixels) x (64*TN channels) block tile
-// would give, or -1 if its LDS footprint does not fit.
+// Whether a (64*TM pixels) x (64*TN channels) block tile fits LDS and gives enough work items (pixel
+// tiles x channel tiles) for two resident blocks per compute unit -- or nearly so where linear tiles
+// are fewer than rectangles would be: 392 tiles in one round beat twice as many half as large.
 template <int TM, int TN, int WPH, bool WDMA = false>
-int64_t blocks_one(int n, int h, int w, int c_in, int c_out)
+bool fills(int n, int h, int w, int c_in, int c_out, bool win)
 {
     ConvGeom g;
     size_t smem;
-    if (!make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, g, smem)) return -1;
-    return (int64_t)g.n_co_tiles * g.n_ptiles;
+    bool lin;
+    if (!pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, g, smem, &lin)) return false;
+    return (int64_t)g.n_co_tiles * g.n_ptiles >= (lin ? 384 : 512);
 }
 
 // Largest block tile that fits LDS and still fills most of the 256 compute units.
@@ -655,16 +797,15 @@ namespace {
 
 // Which block tile launch_wph takes: the largest that fits LDS and still gives two resident
 // blocks per compute unit.  3: 256 x 128, 2: 128 x 128 with streamed weights, 1: 128 x 128,
-// 0: 64 x 64.
+// 0: 64 x 64.  win: a pooled layer (its tiles are made of 2x2 windows).
 template <int WPH>
-int tile_choice_wph(int n, int h, int w, int c_in, int c_out)
+int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win)
 {
-    const int64_t want = 512;     // two resident blocks per compute unit
     // the largest tile keeps its weights resident (WPH <= 4) or streams them by DMA
     constexpr bool WD = WPH >= 8;
-    if (blocks_one<4, 2, WPH, WD>(n, h, w, c_in, c_out) >= want) return 3;
-    if (WD && blocks_one<2, 2, WPH, WD>(n, h, w, c_in, c_out) >= want) return 2;
-    if (blocks_one<2, 2, WPH>(n, h, w, c_in, c_out) >= want) return 1;
+    if (fills<4, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return 3;
+    if (WD && fills<2, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return 2;
+    if (fills<2, 2, WPH>(n, h, w, c_in, c_out, win)) return 1;
     return 0;
 }
 
@@ -673,7 +814,7 @@ bnn_status launch_wph(const uint32_t *in, const uint32_t *wt, int n, int h, int 
                       const EpiArgs &ep, hipStream_t s)
 {
     constexpr bool WD = WPH >= 8;
-    switch (tile_choice_wph<WPH>(n, h, w, c_in, c_out)) {
+    switch (tile_choice_wph<WPH>(n, h, w, c_in, c_out, ep.packed && ep.pool == 2)) {
     case 3: return launch_conv_big_tile<WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
     case 2: return launch_one<2, 2, WPH, WD>(in, wt, n, h, w, c_in, c_out, ep, s);
     case 1: return launch_one<2, 2, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);

@@ -56,37 +56,48 @@ __device__ __forceinline__ void row_to_pixel(int row, const TilePos &p, int &img
 }
 
 // Raw int32 output of one wave's tiles (debug / "no step" path).
-// getx(i, j, r): pre-activation of pixel tile i, channel tile j, register r.
-// row0 = first GEMM row of this wave inside the block, ch0 = first channel of this wave.
-template <int TM, int TN, typename GetX>
-__device__ __forceinline__ void conv_tile_store_preact(GetX getx, int row0, int ch0, int l32, int half,
-                                                       const TilePos &p, int32_t *preact)
+// getx(i, j, r): pre-activation of pixel tile i, channel tile j, register r.  getpix(i): index of the
+// lane's pixel of tile i in the output tensor, or -1.  ch0 = first channel of this wave.
+template <int TM, int TN, typename GetX, typename GetPix>
+__device__ __forceinline__ void conv_store_preact(GetX getx, GetPix getpix, int ch0, int half, int c_out, int32_t *preact)
 {
-    const bool vec_ok = (p.c_out & 3) == 0;
-    // (the address arithmetic below hangs on a value the compiler cannot see through, so that it
-    // stays inside the caller's "raw output requested" branch instead of running for every tile)
-    asm volatile("" : "+v"(l32));
+    const bool vec_ok = (c_out & 3) == 0;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        int img, y, x;
-        row_to_pixel(row0 + i * 32 + l32, p, img, y, x);
-        if (img >= p.n || y >= p.h || x >= p.w) continue;
-        int32_t *dst = preact + (((int64_t)img * p.h + y) * p.w + x) * p.c_out;
+        const int64_t pix = getpix(i);
+        if (pix < 0) continue;
+        int32_t *dst = preact + pix * c_out;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int c = ch0 + j * 32 + q * 8 + half * 4;
-                if (vec_ok && c + 4 <= p.c_out) {
+                if (vec_ok && c + 4 <= c_out) {
                     *reinterpret_cast<int4 *>(dst + c) =
                         make_int4(getx(i, j, q * 4), getx(i, j, q * 4 + 1), getx(i, j, q * 4 + 2), getx(i, j, q * 4 + 3));
                 } else {
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
-                        if (c + k < p.c_out) dst[c + k] = getx(i, j, q * 4 + k);
+                        if (c + k < c_out) dst[c + k] = getx(i, j, q * 4 + k);
                 }
             }
     }
+}
+
+// The same for rectangular tiles; row0 = first GEMM row of this wave inside the block.
+template <int TM, int TN, typename GetX>
+__device__ __forceinline__ void conv_tile_store_preact(GetX getx, int row0, int ch0, int l32, int half,
+                                                       const TilePos &p, int32_t *preact)
+{
+    // (the address arithmetic below hangs on a value the compiler cannot see through, so that it
+    // stays inside the caller's "raw output requested" branch instead of running for every tile)
+    asm volatile("" : "+v"(l32));
+    auto getpix = [&](int i) -> int64_t {
+        int img, y, x;
+        row_to_pixel(row0 + i * 32 + l32, p, img, y, x);
+        return img >= p.n || y >= p.h || x >= p.w ? (int64_t)-1 : ((int64_t)img * p.h + y) * p.w + x;
+    };
+    conv_store_preact<TM, TN>(getx, getpix, ch0, half, p.c_out, preact);
 }
 
 // Block-cooperative: accumulator start values of the block's `nch` channels (first one
@@ -310,6 +321,28 @@ __device__ __forceinline__ CopyLane make_copy_lane(int block_rows, const TilePos
     return c;
 }
 
+// One pixel's BW words of a block, LDS -> global (dst: the first of them; a pixel has cwo words, the
+// block's are numbers blk_word0 ..).
+template <int BW>
+__device__ __forceinline__ void copy_words(const uint32_t *sp, uint32_t *dst, int cwo, int blk_word0)
+{
+    if ((cwo % BW) == 0) {
+        if (BW == 8) {
+            reinterpret_cast<uint4 *>(dst)[0] = reinterpret_cast<const uint4 *>(sp)[0];
+            reinterpret_cast<uint4 *>(dst)[1] = reinterpret_cast<const uint4 *>(sp)[1];
+        } else if (BW == 4) *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(sp);
+        else if (BW == 2) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(sp);
+        else {
+#pragma unroll
+            for (int k = 0; k < BW; ++k) dst[k] = sp[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < BW; ++k)
+            if (blk_word0 + k < cwo) dst[k] = sp[k];
+    }
+}
+
 // blk_word0 = first word index of the block inside a pixel's words.
 template <int BW>
 __device__ __forceinline__ void conv_tile_copy_out(const uint32_t *out_lds, const CopyLane &c, int blk_word0,
@@ -319,26 +352,10 @@ __device__ __forceinline__ void conv_tile_copy_out(const uint32_t *out_lds, cons
     const int cwo = (p.c_out + 31) >> 5;
     const int oh = pool == 2 ? p.h >> 1 : p.h, ow = pool == 2 ? p.w >> 1 : p.w;
     const int oy0 = pool == 2 ? p.y0 >> 1 : p.y0, ox0 = pool == 2 ? p.x0 >> 1 : p.x0;
-    const bool vec_ok = (cwo % BW) == 0;
     if (c.active && p.img0 + c.il < p.n && oy0 + c.ty < oh && ox0 + c.tx < ow) {
         // the origin's part of the address is the same for every thread
         uint32_t *dst = ep.packed + ((((int64_t)p.img0 * oh + oy0) * ow + ox0) * cwo + blk_word0) + c.rel;
-        const uint32_t *sp = out_lds + c.src * BW;
-        if (vec_ok) {
-            if (BW == 8) {
-                reinterpret_cast<uint4 *>(dst)[0] = reinterpret_cast<const uint4 *>(sp)[0];
-                reinterpret_cast<uint4 *>(dst)[1] = reinterpret_cast<const uint4 *>(sp)[1];
-            } else if (BW == 4) *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(sp);
-            else if (BW == 2) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(sp);
-            else {
-#pragma unroll
-                for (int k = 0; k < BW; ++k) dst[k] = sp[k];
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < BW; ++k)
-                if (blk_word0 + k < cwo) dst[k] = sp[k];
-        }
+        copy_words<BW>(out_lds + c.src * BW, dst, cwo, blk_word0);
     }
 }
 

@@ -236,6 +236,41 @@ def test_conv_binary_closed_form_borders():
     assert r[0, h - 1, w - 1, co - 1] == -c
 
 
+# Images whose sizes leave rectangular pixel tiles half empty, in batches large enough for the tile
+# kernels to take tiles in raster order instead: every channel width, resident and streamed weights,
+# the three block tiles, windows and pixels, tiles that span many images or part of a row.
+@pytest.mark.parametrize("n,h,w,ci,co", [(200, 17, 17, 224, 96), (1137, 7, 7, 320, 72), (300, 21, 21, 64, 40),
+                                         (600, 10, 10, 128, 128), (2100, 6, 6, 512, 128), (520, 3, 3, 1024, 2048),
+                                         (9000, 3, 3, 32, 32), (100, 9, 9, 160, 64), (40, 20, 100, 64, 33),
+                                         (130, 18, 34, 99, 70)])
+def test_conv_binary_raster_tiles(n, h, w, ci, co):
+    print("conv raster", n, h, w, ci, co, flush=True)
+    rng = rng_of(n + 3 * h + 5 * w + 7 * ci + co)
+    x, wt = pm1(rng, (n, h, w, ci)), pm1(rng, (co, 3, 3, ci))
+    want = oracle.conv2d(x, wt, 1, -1)
+    cw = (ci + 31) // 32
+    xd, wd = dev(pack_pm1(x)), dev(pack_pm1(wt.reshape(co * 9, ci)).reshape(co, 3, 3, cw))
+    raw = fill_i32((n + 1, h, w, co), 4242)
+    P.bnn_conv_binary(xd, n, h, w, ci, wd, co, preact_out=raw)
+    np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
+    assert int((raw[n] != 4242).sum()) == 0
+    thr = want[n // 2, h // 2, w // 2].copy()                  # ties
+    thr[::2] = rng.integers(-(9 * ci // 8) - 1, 9 * ci // 8 + 2, size=thr[::2].size)
+    flip = rng.integers(0, 2, size=co).astype(np.uint8)
+    s = oracle.step(want, thr, flip)
+    forms = [(1, 0, s)]
+    if h % 2 == 0 and w % 2 == 0:
+        forms += [(2, 0, oracle.maxpool2(s)), (2, 1, oracle.step(oracle.maxpool2(want), thr, flip))]
+    for pool, pool_first, ref in forms:
+        pk = fill_i32((n + 1, h // pool, w // pool, (co + 31) // 32), -1)
+        raw.fill_(4242)
+        P.bnn_conv_binary(xd, n, h, w, ci, wd, co, thr=dev(thr), flip=dev(flip), pool=pool, pool_first=pool_first,
+                          preact_out=raw, packed_out=pk)
+        np.testing.assert_array_equal(host_u32(pk[:n]), pack_pm1(ref), err_msg=f"pool {pool} {pool_first}")
+        assert int((pk[n] != -1).sum()) == 0
+        np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
+
+
 # ------------------------------------------------------------------- conv_first_int8
 FIRST_SHAPES = [(2, 28, 28, 1, 64, 3, 3, 1, -1, 2), (2, 32, 32, 3, 128, 3, 3, 1, -1, 1),
                 (64, 1, 1, 784, 512, 1, 1, 0, -1, 1), (3, 8, 8, 3, 32, 3, 3, 1, 0, 2),
