@@ -50,6 +50,23 @@ def test_pack_bits_general_int8_values():
         np.testing.assert_array_equal(host_u32(pack_on_gpu(a)), pack_pm1(a))
 
 
+def test_default_stream_argument_is_torchs_current_stream():
+    import threading
+    from paper_2301_05126_amd import api
+    src = torch.ones((1, 64), dtype=torch.int8, device=DEV)
+    P.bnn_pack_bits(src, 1, 64, empty_i32(2))                # first call: the documented way
+    assert api._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    seen = []
+    with torch.cuda.stream(side):
+        assert api._stream(None) == side.cuda_stream
+        th = threading.Thread(target=lambda: seen.append((api._stream(None), torch.cuda.current_stream().cuda_stream)))
+        th.start()
+        th.join()
+    assert seen[0][0] == seen[0][1]                          # a stream context belongs to its thread
+    assert api._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
 # --------------------------------------------------------------- threshold/sign/pool
 @pytest.mark.parametrize("n,h,w,c", [(2, 4, 6, 8), (1, 2, 2, 3), (3, 6, 6, 40), (2, 8, 8, 64),
                                      (1, 28, 28, 64), (2, 4, 4, 33), (1, 16, 16, 256), (5, 2, 2, 130)])
