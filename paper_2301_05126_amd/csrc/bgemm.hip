@@ -76,6 +76,7 @@ __device__ __forceinline__ void pin_acc(v16f &acc) { asm volatile("" : "+a"(acc)
 struct GemmWalk {
     int nbm, nbn;            // tiles along M and N
     int tiles;               // nbm * nbn
+    int stream;              // 1: streaming stores of raw sums
 };
 
 // Persistent blocks.  Tile numbers run column-major inside bands of eight tile rows; each XCD takes
@@ -96,7 +97,7 @@ struct GemmWalk {
 // and staging through registers), and the power limit, which holds the clock at 1.9 GHz; then the
 // stores of raw sums, 256 KB per tile and compute unit, in which the matrix pipe idles (9.4 us
 // where all compute units store at once, the chip's write bandwidth; 5.7 us otherwise).  Before and
-// after, us: 16384^3 1592 / 1408, 8192^3 216 / 200, 4096^3 35.2 / 34.5 (a single round: 9.4 of its 34 us
+// after, us: 16384^3 1518 / 1361, 8192^3 210 / 193, 4096^3 34.4 / 31.7 (a single round: 9 of its 32 us
 // are the stores), step output at 5000 x 5000 x 10000 194 / 107, 4096 x 1024 x 8192 19.3 / 14.7.
 //
 // An LDS row is four 16-byte units; unit u of row r sits at position u ^ ((r >> 1) & 3), so that the
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
     constexpr int ROWS_I = VEC == 4 ? 16 : 4;     // rows that one transfer fills
     constexpr int BUF = (BM + BN) * KC;           // words of one buffer: A's rows, then B's
     constexpr int NST = TM * TN * 4;              // 16-byte stores of a wave's tile
+    constexpr int GJ = TM * TN >= 16 ? TN : 1;    // column tiles whose raw sums are stored together
     constexpr int AHEAD = NBUF - 1;               // chunks requested ahead
     constexpr int YOUNGER = (AHEAD - 2) * IPC;    // transfers younger than the chunk that is waited for
     static_assert(IPC <= 32, "the wait counter holds at most 63 transfers");
@@ -340,41 +342,46 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (!PACKED) pin_acc(acc[i][j]);
+                for (int j0 = 0; j0 < TN; j0 += GJ) {
+                    v4i x[GJ][4];                  // a row's GJ * 128 bytes leave one after the other
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<int4 *>(wr[q]) = make_int4((int)acc[i][j][q * 4], (int)acc[i][j][q * 4 + 1],
-                                                                     (int)acc[i][j][q * 4 + 2], (int)acc[i][j][q * 4 + 3]);
-                    // (other lanes of the wave read what this one wrote: LDS keeps a wave's order)
-                    asm volatile("" ::: "memory");
-                    v4i x[4];
+                    for (int j = 0; j < GJ; ++j) {
+                        v16f &ac = acc[i][j0 + j];
+                        if (!PACKED) pin_acc(ac);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) x[k] = *reinterpret_cast<const v4i *>(rp + k * 256);
-                    asm volatile("" ::: "memory");
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<int4 *>(wr[q]) =
+                                make_int4((int)ac[q * 4], (int)ac[q * 4 + 1], (int)ac[q * 4 + 2], (int)ac[q * 4 + 3]);
+                        // (other lanes of the wave read what this one wrote: LDS keeps a wave's order)
+                        asm volatile("" ::: "memory");
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) x[j][k] = *reinterpret_cast<const v4i *>(rp + k * 256);
+                        asm volatile("" ::: "memory");
+                        __builtin_amdgcn_sched_barrier(0);      // one tile's registers at a time
+                    }
                     if (whole) {
-                        const unsigned aj = col + j * 32 < (unsigned)N ? at + j * 128 : 0x80000000u;
-                        // streaming stores, unless a row's 128 bytes lie in two cache lines (6000 x 6001, K = 4096:
-                        // 147 us with streaming stores, 81 us without)
-                        if ((N & 31) == 0) {
 #pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                __builtin_amdgcn_raw_buffer_store_b128(x[k], crs, aj + k * 8 * c_row, 0, 2);
-                        } else {
+                        for (int k = 0; k < 4; ++k)
 #pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                __builtin_amdgcn_raw_buffer_store_b128(x[k], crs, aj + k * 8 * c_row, 0, 0);
-                        }
+                            for (int j = 0; j < GJ; ++j) {
+                                const int jj = j0 + j;
+                                const unsigned aj = (col + jj * 32 < (unsigned)N ? at + jj * 128 : 0x80000000u) + k * 8 * c_row;
+                                if (gw.stream) __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 2);
+                                else __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 0);
+                            }
                     } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const unsigned ae = col + j * 32 + e < (unsigned)N ? at + (j * 128 + e * 4) : 0x80000000u;
+                        for (int j = 0; j < GJ; ++j)
 #pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                __builtin_amdgcn_raw_buffer_store_b32(x[k][e], crs, ae + k * 8 * c_row, 0, 0);
-                        }
+                            for (int e = 0; e < 4; ++e) {
+                                const int jj = j0 + j;
+                                const unsigned ae = col + jj * 32 + e < (unsigned)N ? at + (jj * 128 + e * 4) : 0x80000000u;
+#pragma unroll
+                                for (int k = 0; k < 4; ++k)
+                                    __builtin_amdgcn_raw_buffer_store_b32(x[j][k][e], crs, ae + k * 8 * c_row, 0, 0);
+                            }
                     }
-                    __builtin_amdgcn_sched_barrier(0);      // one tile's registers at a time
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 at += 32 * c_row;
             }
@@ -723,6 +730,10 @@ bnn_status launch_mfma(const uint32_t *a, int64_t m, int64_t k, const uint32_t *
     const int64_t tiles = nbm * nbn;
     if (tiles > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;
     gw.nbm = (int)nbm; gw.nbn = (int)nbn; gw.tiles = (int)tiles;
+    // Streaming stores of raw sums, only of whole cache lines (6000 x 6001, K = 4096: 147 us with them, 81
+    // without).  The 256 x 256 tile: where C is larger than the 256 MiB memory-side cache (12000 x 8000,
+    // K = 1024: 84.5 us with, 88.5 without; 8000 x 8000, K = 512: 54 with, 48 without).
+    gw.stream = (n & 31) == 0 && (TM * TN < 16 || m * n > (int64_t)1 << 26);
     if ((kw & 3) == 0) return launch_mfma_vec<TM, TN, 4>(a, m, k, b, n, kw, gw, ep, s);
     return launch_mfma_vec<TM, TN, 1>(a, m, k, b, n, kw, gw, ep, s);
 }
