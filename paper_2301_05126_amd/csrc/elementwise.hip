@@ -1,6 +1,7 @@
 // Bandwidth-bound helpers for gfx950: bit packing of +-1 values, and the stand-alone
 // step (+ 2x2 max-pool) layer on int32 pre-activations (paper Sec. II-A step / maxpool).
 #include "bnn_internal.h"
+#include "conv_epilogue.h"
 
 namespace bnn {
 
@@ -37,96 +38,190 @@ __global__ __launch_bounds__(256) void pack_bits_fast(const uint4 *__restrict__ 
     }
 }
 
-// any k: one thread per output word, byte loads.
-__global__ __launch_bounds__(256) void pack_bits_generic(const int8_t *__restrict__ src, int64_t rows,
-                                                         int64_t k, int64_t kw, uint32_t *__restrict__ dst)
+// 16 bytes at any byte address (the compiler may not assume more; the hardware takes it in one load).
+__device__ __forceinline__ uint4 load16_unaligned(const void *p)
 {
-    const int64_t total = rows * kw;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
-        const int64_t r = i / kw, wi = i - r * kw;
-        const int64_t k0 = wi * 32;
-        const int8_t *p = src + r * k + k0;
-        const int cnt = (int)((k - k0) < 32 ? (k - k0) : 32);
-        unsigned word = 0;
-        for (int q = 0; q < cnt; ++q) word |= (p[q] > 0 ? 1u : 0u) << q;
-        dst[i] = word;
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
+// Any k: a row is 2 * kw half words of 16 source bytes, the last one or two of them short or empty;
+// one 16-byte load per lane (at any byte address) and two lanes per word, as above.  Lanes follow
+// the rows' bytes, so that a wave reads about 1 KB in one piece whatever k is.  A block takes
+// HALVES consecutive half words: its first row is found with one division, a lane's row with a
+// multiply-high.  (A tensor of fewer than 16 bytes goes to pack_bits_tiny.)  HBM-bound: 16384 x 5000 values 143 us with a thread per word and byte loads
+// (0.65 TB/s), 16.0 us now (5.8 TB/s); 23804 x 773 42.6 / 5.9 us.
+constexpr int PACK_UNROLL = 4, PACK_HALVES = 256 * PACK_UNROLL;
+
+__global__ __launch_bounds__(256) void pack_bits_ragged(const int8_t *__restrict__ src, int64_t rows, int64_t k,
+                                                        int64_t halves, unsigned mg, uint32_t *__restrict__ dst)
+{
+    const int64_t total = rows * halves;
+    const int8_t *end = src + rows * k;
+    for (int64_t base = (int64_t)blockIdx.x * PACK_HALVES; base < total; base += (int64_t)gridDim.x * PACK_HALVES) {
+        const int64_t row0 = base / halves;
+        const int64_t off0 = base - row0 * halves;
+        const int8_t *p0 = src + row0 * k;
+        uint4 v[PACK_UNROLL];
+        int cnt[PACK_UNROLL], back[PACK_UNROLL];
+#pragma unroll
+        for (int u = 0; u < PACK_UNROLL; ++u) {
+            const int64_t j = off0 + u * 256 + threadIdx.x;
+            // (a block's span of a long row meets at most one more)
+            const int r = halves >= PACK_HALVES ? (j >= halves ? 1 : 0) : div_by((int)j, (int)halves, mg);
+            const int64_t at = (j - r * halves) * 16;                 // first byte inside the row
+            const int8_t *p = p0 + r * k + at;
+            const int64_t left = base + u * 256 + threadIdx.x < total ? k - at : 0;
+            cnt[u] = left >= 16 ? 16 : (left > 0 ? (int)left : 0);
+            // (a load that would pass the tensor's end reads its last 16 bytes, and `back` bytes of them
+            // are shifted out below; a half word without bytes reads the same)
+            const int8_t *lp = cnt[u] > 0 && end - p >= 16 ? p : end - 16;
+            back[u] = cnt[u] > 0 ? (int)(p - lp) : 0;
+            v[u] = load16_unaligned(lp);
+        }
+#pragma unroll
+        for (int u = 0; u < PACK_UNROLL; ++u) {
+            // (bytes behind the row's end belong to the next row)
+            const unsigned bits = (positive_bits16(v[u]) >> back[u]) & ((1u << cnt[u]) - 1u);
+            const unsigned other = __shfl_xor(bits, 1);
+            const int64_t i = base + u * 256 + threadIdx.x;
+            if (i < total && (threadIdx.x & 1) == 0) dst[i >> 1] = bits | (other << 16);
+        }
     }
 }
 
+// At most 15 values in all: one thread.
+__global__ void pack_bits_tiny(const int8_t *__restrict__ src, int rows, int k, uint32_t *__restrict__ dst)
+{
+    for (int r = 0; r < rows; ++r) {
+        unsigned word = 0;
+        for (int q = 0; q < k; ++q) word |= (src[r * k + q] > 0 ? 1u : 0u) << q;
+        dst[r] = word;
+    }
+}
+
+// Stand-alone step (+ pool).  A thread owns one group of eight channels, whose thresholds and flips
+// it reads once, and walks over output pixels; four neighbouring lanes own a word.  A block's threads
+// cover `gb` groups of 256 / gb pixels at a time, gb = min(groups per pixel, 256); the second grid index takes
+// further groups (the grid is bx x by blocks in one dimension).  Output pixel p of a pooled layer is (q, x) with q = image and output row in one,
+// and its window starts at input row 2q, column 2x: no other index is ever taken apart, and the step
+// to the thread's next pixel is a fixed (q, x) increment.  HBM-bound.  Before, an item's four 64-bit
+// divisions, eight flip bytes and eight thresholds were worked out and read anew for each pixel; us,
+// before / after (at 6 TB/s): 256 x 32 x 32 x 128 77 / 24 (23), with pooling 35 / 23 (23);
+// 1182 x 6 x 6 x 120 15.3 / 6.0 (3.5); 500 x 16 x 16 x 511 248 / 64 (45).
 struct StepGeom {
-    int n, h, w, c;
-    int ho, wo, cwo, pool, pool_first;
+    int64_t pixels;                  // output pixels
+    int w, c, wo, cwo, gb;
+    int pool_first;
+    int64_t step_q;                  // a grid's worth of pixels as a (q, x) increment
+    int step_x;
+    int bx;
+    unsigned mg_wo;                  // magic_floor of wo
 };
 
-// One thread per (output pixel, 8-channel group); four neighbouring lanes own one word.
-template <bool VEC>
+template <int POOL, int U>                                       // U: pixels of a thread in flight together
 __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restrict__ x,
                                                         const int32_t *__restrict__ thr,
                                                         const uint8_t *__restrict__ flip, StepGeom g,
                                                         uint32_t *__restrict__ out)
 {
-    const int gpp = g.cwo * 4;                                   // 8-channel groups per pixel
-    const int64_t total = (int64_t)g.n * g.ho * g.wo * gpp;      // multiple of 4
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += stride) {
-        const int64_t idx = base + threadIdx.x;
-        unsigned byte = 0;
-        if (idx < total) {
-            const int grp = (int)(idx % gpp);
-            int64_t p = idx / gpp;
-            const int xo = (int)(p % g.wo); p /= g.wo;
-            const int yo = (int)(p % g.ho);
-            const int img = (int)(p / g.ho);
-            const int c0 = grp * 8;
-            if (c0 < g.c) {
-                int t[8];
-                unsigned fm = 0, valid = 0;
+    constexpr int WIN = POOL * POOL;
+    static_assert(POOL == 1 || U == 1, "a pooled pixel has eight loads of its own");
+    const int t = threadIdx.x, ppb = 256 / g.gb;
+    const int slot = t / g.gb;
+    const int yb = (int)blockIdx.x / g.bx, xb = (int)blockIdx.x - yb * g.bx;
+    const int grp = yb * 256 + (t - slot * g.gb);
+    if (slot >= ppb) return;                                     // (whole quads of lanes: gb is a multiple of 4)
+    const int c0 = grp * 8;
+    const int nc = g.c - c0 < 8 ? g.c - c0 : 8;                  // channels of the group that exist (may be <= 0)
+    if (grp >= g.cwo * 4) return;                                // (whole quads again)
+    // thresholds and flips: three wide loads for a whole group (sixteen narrow gathers per thread made
+    // the address unit the bound of small layers); channels that do not exist get a threshold that is
+    // never exceeded
+    int tv[8];
+    unsigned fm = 0;
+    if (nc == 8) {
+        const int4 a = *reinterpret_cast<const int4 *>(thr + c0), b = *reinterpret_cast<const int4 *>(thr + c0 + 4);
+        uint64_t fl = 0;
+        if (flip) __builtin_memcpy(&fl, flip + c0, 8);
+        tv[0] = a.x; tv[1] = a.y; tv[2] = a.z; tv[3] = a.w;
+        tv[4] = b.x; tv[5] = b.y; tv[6] = b.z; tv[7] = b.w;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const bool ok = c0 + j < g.c;
-                    t[j] = ok ? thr[c0 + j] : 0;
-                    if (ok) valid |= 1u << j;
-                    if (ok && flip && flip[c0 + j]) fm |= 1u << j;
-                }
-                int vmax[8];
+        for (int j = 0; j < 8; ++j) fm |= ((fl >> (8 * j)) & 0xff ? 1u : 0u) << j;
+    } else {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) vmax[j] = INT32_MIN;
-                for (int sy = 0; sy < g.pool; ++sy)
-                    for (int sx = 0; sx < g.pool; ++sx) {
-                        const int y = yo * g.pool + sy, xx = xo * g.pool + sx;
-                        const int32_t *src = x + (((int64_t)img * g.h + y) * g.w + xx) * g.c + c0;
-                        int v[8];
-                        if (VEC) {
-                            const int4 v0 = *reinterpret_cast<const int4 *>(src);
-                            const int4 v1 = *reinterpret_cast<const int4 *>(src + 4);
-                            v[0] = v0.x; v[1] = v0.y; v[2] = v0.z; v[3] = v0.w;
-                            v[4] = v1.x; v[5] = v1.y; v[6] = v1.z; v[7] = v1.w;
-                        } else {
+        for (int j = 0; j < 8; ++j) {
+            tv[j] = j < nc ? thr[c0 + j] : INT32_MAX;
+            if (flip && j < nc && flip[c0 + j]) fm |= 1u << j;
+        }
+    }
+    int64_t p = (int64_t)xb * ppb + slot;
+    const int64_t stride = (int64_t)g.bx * ppb;
+    int64_t q = 0;
+    int xo = 0;
+    if (POOL == 2) {
+        q = g.pixels < (int64_t)1 << 31 ? div_by((int)p, g.wo, g.mg_wo) : p / g.wo;
+        xo = (int)(p - q * g.wo);
+    }
+    auto load8 = [&](const int32_t *src, int (&v)[8]) {
+        if (nc == 8) {
+            const uint4 a = load16_unaligned(src), b = load16_unaligned(src + 4);
+            v[0] = (int)a.x; v[1] = (int)a.y; v[2] = (int)a.z; v[3] = (int)a.w;
+            v[4] = (int)b.x; v[5] = (int)b.y; v[6] = (int)b.z; v[7] = (int)b.w;
+        } else {
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) v[j] = (c0 + j < g.c) ? src[j] : 0;
-                        }
-                        unsigned b = 0;
+            for (int j = 0; j < 8; ++j) v[j] = j < nc ? src[j] : INT32_MIN;
+        }
+    };
+    auto step8 = [&](const int (&v)[8]) {
+        unsigned b = 0;
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            b |= (v[j] > t[j] ? 1u : 0u) << j;
-                            vmax[j] = max(vmax[j], v[j]);
-                        }
-                        byte |= (b ^ fm) & valid;
-                    }
-                if (g.pool_first) {
-                    // paper order: max of the window's pre-activations, then the step
-                    unsigned b = 0;
+        for (int j = 0; j < 8; ++j) b |= (v[j] > tv[j] ? 1u : 0u) << j;
+        return b ^ fm;
+    };
+    for (; p < g.pixels; p += stride * U) {
+        int v[U][WIN][8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) b |= (vmax[j] > t[j] ? 1u : 0u) << j;
-                    byte = (b ^ fm) & valid;
-                }
+        for (int u = 0; u < U; ++u) {
+            if (POOL == 1) {
+                // (a pixel past the end reads the last one and is not stored)
+                const int64_t pu = p + u * stride;
+                load8(x + (pu < g.pixels ? pu : g.pixels - 1) * g.c + c0, v[u][0]);
+            } else {
+                const int32_t *src = x + (2 * q * g.w + 2 * xo) * g.c + c0;
+                load8(src, v[u][0]);
+                load8(src + g.c, v[u][1 % WIN]);
+                load8(src + (int64_t)g.w * g.c, v[u][2 % WIN]);
+                load8(src + (int64_t)(g.w + 1) * g.c, v[u][3 % WIN]);
             }
         }
-        unsigned word = byte << (8 * (threadIdx.x & 3));
-        word |= __shfl_xor(word, 1);
-        word |= __shfl_xor(word, 2);
-        if (idx < total && (threadIdx.x & 3) == 0) out[idx >> 2] = word;
+        if (POOL == 2) {
+            xo += g.step_x;
+            q += g.step_q;
+            if (xo >= g.wo) { xo -= g.wo; ++q; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            unsigned byte;
+            if (POOL == 1) {
+                byte = step8(v[u][0]);
+            } else if (g.pool_first) {
+                // paper order: max of the window's pre-activations, then the step
+                int m[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    m[j] = max(max(v[u][0][j], v[u][1 % WIN][j]), max(v[u][2 % WIN][j], v[u][3 % WIN][j]));
+                byte = step8(m);
+            } else {
+                byte = step8(v[u][0]) | step8(v[u][1 % WIN]) | step8(v[u][2 % WIN]) | step8(v[u][3 % WIN]);
+            }
+            unsigned word = byte << (8 * (t & 3));
+            word |= __shfl_xor(word, 1);
+            word |= __shfl_xor(word, 2);
+            const int64_t pu = p + u * stride;
+            if (pu < g.pixels && (t & 3) == 0) out[pu * g.cwo + (grp >> 2)] = word;
+        }
     }
 }
 
@@ -150,8 +245,15 @@ bnn_status launch_pack_bits(const int8_t *src, int64_t rows, int64_t k, uint32_t
         hipLaunchKernelGGL(pack_bits_fast, dim3(grid_for(n_half)), dim3(256), 0, s,
                            reinterpret_cast<const uint4 *>(src), n_half, dst);
     } else {
-        hipLaunchKernelGGL(pack_bits_generic, dim3(grid_for(rows * kw)), dim3(256), 0, s, src, rows, k, kw,
-                           dst);
+        if (rows * k < 16) {
+            hipLaunchKernelGGL(pack_bits_tiny, dim3(1), dim3(1), 0, s, src, (int)rows, (int)k, dst);
+            return hip_result(hipGetLastError());
+        }
+        const int64_t halves = 2 * kw;
+        int64_t blocks = (rows * halves + PACK_HALVES - 1) / PACK_HALVES;
+        if (blocks > 256 * 32) blocks = 256 * 32;
+        hipLaunchKernelGGL(pack_bits_ragged, dim3((unsigned)blocks), dim3(256), 0, s, src, rows, k, halves,
+                           halves < PACK_HALVES ? magic_floor((int)halves) : 0u, dst);
     }
     return hip_result(hipGetLastError());
 }
@@ -162,13 +264,27 @@ bnn_status launch_threshold_sign_maxpool(const int32_t *x, int n, int h, int w, 
 {
     if (n == 0) return BNN_OK;
     StepGeom g;
-    g.n = n; g.h = h; g.w = w; g.c = c;
-    g.pool = pool; g.pool_first = pool_first; g.ho = h / pool; g.wo = w / pool; g.cwo = (c + 31) / 32;
-    const int64_t total = (int64_t)n * g.ho * g.wo * g.cwo * 4;
-    if ((c & 7) == 0)
-        hipLaunchKernelGGL(step_pool_kernel<true>, dim3(grid_for(total)), dim3(256), 0, s, x, thr, flip, g, out);
-    else
-        hipLaunchKernelGGL(step_pool_kernel<false>, dim3(grid_for(total)), dim3(256), 0, s, x, thr, flip, g, out);
+    const int ho = h / pool;
+    g.w = w; g.c = c; g.wo = w / pool; g.cwo = (c + 31) / 32; g.pool_first = pool_first;
+    g.pixels = (int64_t)n * ho * g.wo;
+    const int gpp = g.cwo * 4;
+    g.gb = gpp < 256 ? gpp : 256;
+    const int ppb = 256 / g.gb;
+    // four pixels per thread in flight where that still leaves a block for every compute unit
+    const bool four = pool == 1 && g.pixels >= (int64_t)ppb * 4 * 256;
+    int64_t bx = (g.pixels + ppb * (four ? 4 : 1) - 1) / (ppb * (four ? 4 : 1));
+    const int64_t by = (gpp + 255) / 256;
+    const int64_t cap = by < 256 * 16 ? 256 * 16 / by : 1;      // blocks per compute unit, pixels strided beyond
+    if (bx > cap) bx = cap;
+    const int64_t stride = bx * ppb;
+    g.step_q = stride / g.wo;
+    g.step_x = (int)(stride - g.step_q * g.wo);
+    g.bx = (int)bx;
+    g.mg_wo = magic_floor(g.wo);
+    const dim3 grid((unsigned)(bx * by));
+    if (four) hipLaunchKernelGGL((step_pool_kernel<1, 4>), grid, dim3(256), 0, s, x, thr, flip, g, out);
+    else if (pool == 1) hipLaunchKernelGGL((step_pool_kernel<1, 1>), grid, dim3(256), 0, s, x, thr, flip, g, out);
+    else hipLaunchKernelGGL((step_pool_kernel<2, 1>), grid, dim3(256), 0, s, x, thr, flip, g, out);
     return hip_result(hipGetLastError());
 }
 

@@ -50,6 +50,19 @@ def test_pack_bits_general_int8_values():
         np.testing.assert_array_equal(host_u32(pack_on_gpu(a)), pack_pm1(a))
 
 
+# Rows that are no whole number of words: every byte alignment of a row start, tensors shorter than
+# one 16-byte load, rows around the block's span of 1024 half words (16 KB), more rows than a grid.
+@pytest.mark.parametrize("rows,k", [(1, 15), (5, 3), (16, 1), (1, 17), (2, 31), (3, 47), (9, 49), (1031, 33), (333, 95),
+                                    (7, 16351), (5, 16383), (3, 16417), (2, 40001), (70001, 129)])
+def test_pack_bits_ragged_rows(rows, k):
+    print("pack ragged", rows, k, flush=True)
+    a = rng_of(rows + 7 * k).integers(-128, 128, size=(rows, k), dtype=np.int8)
+    dst = fill_i32((rows + 1, (k + 31) // 32), -1)
+    P.bnn_pack_bits(dev(a), rows, k, dst)
+    np.testing.assert_array_equal(host_u32(dst[:rows]), pack_pm1(a))
+    assert int((dst[rows] != -1).sum()) == 0
+
+
 def test_default_stream_argument_is_torchs_current_stream():
     import threading
     from paper_2301_05126_amd import api
@@ -92,6 +105,32 @@ def test_threshold_sign_maxpool(n, h, w, c, pool, use_flip):
         P.bnn_threshold_sign_maxpool(dev(x), n, h, w, c, dev(thr), dev(flip) if use_flip else None, 2, out2,
                                      pool_first=1)
         np.testing.assert_array_equal(host_u32(out2), pack_pm1(oracle.step(oracle.maxpool2(x), thr, flip)))
+
+
+# One and several pixels per thread, groups of eight channels that are short or missing, words that
+# end inside a quad of lanes, more groups than a block has threads, extreme sums and thresholds, and
+# flips at an odd address.
+@pytest.mark.parametrize("n,h,w,c", [(1, 2, 2, 1), (3, 6, 10, 9), (5, 14, 18, 72), (40, 30, 26, 100), (300, 16, 16, 33),
+                                     (130, 32, 32, 64), (2, 4, 6, 2047), (2, 2, 4, 2056), (1, 2, 2, 5000)])
+@pytest.mark.parametrize("pool,pool_first", [(1, 0), (2, 0), (2, 1)])
+def test_threshold_sign_maxpool_groups(n, h, w, c, pool, pool_first):
+    print("step groups", n, h, w, c, pool, pool_first, flush=True)
+    rng = rng_of(n + 3 * h + 5 * w + 7 * c)
+    x = rng.integers(-9, 10, size=(n, h, w, c)).astype(np.int32)
+    lim = np.iinfo(np.int32)
+    x[0, 0, 0, :] = lim.min
+    x[-1, -1, -1, :] = lim.max
+    thr = rng.integers(-4, 5, size=c).astype(np.int32)
+    thr[::5], thr[1::7] = lim.max, lim.min
+    flip = rng.integers(0, 3, size=c).astype(np.uint8)               # any non-zero byte flips
+    odd = dev(np.concatenate([np.zeros(1, np.uint8), flip]))[1:]
+    out = fill_i32((n + 1, h // pool, w // pool, (c + 31) // 32), -1)
+    P.bnn_threshold_sign_maxpool(dev(x), n, h, w, c, dev(thr), odd, pool, out, pool_first=pool_first)
+    f = (flip != 0).astype(np.uint8)
+    want = (oracle.step(oracle.maxpool2(x), thr, f) if pool_first else
+            oracle.maxpool2(oracle.step(x, thr, f)) if pool == 2 else oracle.step(x, thr, f))
+    np.testing.assert_array_equal(host_u32(out[:n]), pack_pm1(want))
+    assert int((out[n] != -1).sum()) == 0
 
 
 # ------------------------------------------------------------------------- fc_binary
