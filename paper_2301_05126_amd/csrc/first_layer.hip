@@ -4,12 +4,15 @@
 // (paper Sec. II-A convolutional layer applied to the 8-bit input image; with
 // kh = kw = h = w = 1 it is the fully-connected first layer of an MLP).
 //
-// Five kernels, picked by shape:
+// Six kernels, picked by shape:
 //   conv_first_small  at most 6144 tiles of 32 pixels x 32 channels, kernel height <= 4, kernel rows of <= 16 bytes:
 //                     one wave per 32 pixels x 32 channels, operands straight from global
 //                     memory, the step in registers (latency: batch 1 .. 8 of a small image).
 //   conv_first_img    3x3, one ring of padding, <= 4 channels, power-of-two width: whole images
 //                     in LDS, persistent blocks (throughput: large batches of small images).
+//   conv_first_lin    kernel rows of <= 32 bytes, at most 14 16-byte units, over images of any size:
+//                     256 output pixels in raster order per tile, the input rows they touch in LDS as
+//                     they lie in memory.
 //   conv_first_mfma   small kernels (kh * roundup16(kw*c_in) <= 128 bytes per pixel): the int8
 //                     input patch and the block's weights live in LDS; each lane gathers 16
 //                     contiguous patch bytes (one kernel row of one pixel) per MFMA operand
@@ -29,6 +32,7 @@
 // window and OR their bit words.
 #include "bnn_internal.h"
 #include "conv_epilogue.h"
+#include "lds_dma.h"
 
 namespace bnn {
 
@@ -158,7 +162,6 @@ __global__ __launch_bounds__(256) void conv_first_kernel(const int8_t *__restric
 }
 
 // ------------------------------------------------------------------ matrix-core kernels
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 struct FirstGeomM {
@@ -750,6 +753,246 @@ __global__ __launch_bounds__(256, 4) void conv_first_img(const int8_t *__restric
     }
 }
 
+__device__ __forceinline__ unsigned bytes_below(int t)      // mask of the bytes b < t of a dword
+{
+    return t <= 0 ? 0u : (t >= 4 ? 0xffffffffu : (1u << (8 * t)) - 1u);
+}
+
+// ---- kernel rows of at most 32 bytes over images of any size: tiles in raster order.
+//
+// A tile is the next 256 output pixels (64 windows when pooling) of the batch, so images of any size
+// fill their tiles (18 x 18 images give 324 rows of the implicit GEMM each, 1024 with 16 x 16
+// rectangles).  The input rows that they touch are one contiguous range of the tensor, whichever
+// images they lie in; it goes to LDS as it is, global -> LDS without registers or index arithmetic,
+// one tile ahead.  What lies outside an image is settled where the operands are gathered: a kernel
+// row above or below it reads a few bytes of pad value instead, and the columns left and right of it
+// are replaced under a byte mask that depends on the output column only (a table in LDS).  Weights
+// resident, MFMA, epilogue and deferred copy-out as in conv_first_img; K = [kernel row][its bytes,
+// padded to 16 * U16], a K step = two 16-byte units, one per lane half.
+//
+// What bounds it is the vector ALU: some 60 instructions per 32 pixels for their places and operands
+// and 45 per 32 x 32 outputs for the step.  Against rectangles (conv_first_mfma) or v_dot4
+// (conv_first_kernel, kernel rows of more than 16 bytes), us: 937 x 18 x 18 x 3 -> 192, 5x5 62.9 / 19.7;
+// 145 x 50 x 50 x 3 -> 256, 5x5 45.1 / 23.3; 500 x 30 x 30 x 3 -> 100, 3x3 18.4 / 14.8; 2000 x 28 x 28 x 1
+// -> 64, 3x3 23.7 / 20.5; 100 x 40 x 40 x 4 -> 128, 5x5 (v_dot4) 84 / 11.4.
+struct FirstGeomL {
+    int n, h, w, c_in, c_out, kh, kw, pad, pad_value;
+    int wo, sl, rowb;                // output columns, bytes of a kernel row, of an image row
+    int win, upi, ww;                // 1: a unit is a 2x2 window; units per image, per row of units
+    int n_tiles, step_img, step_u;   // tiles; a grid's worth of tiles as an (image, unit) increment
+    int front, cap;                  // LDS bytes before a patch, of a patch (multiples of 16)
+    int64_t total;                   // bytes of the input
+    unsigned mg_upi, mg_ww;          // magic_floor
+};
+
+template <int NG, int NS, int U16>
+__global__ __launch_bounds__(256, 4) void conv_first_lin(const int8_t *__restrict__ in, const int8_t *__restrict__ wt,
+                                                         FirstGeomL g, EpiArgs ep, ClearArgs clr)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    clear_words(clr);
+    constexpr int TN = 2, BW = 2 * NG, WS = NS * 32 + 16, NU = 2 * NS;
+    unsigned char *Wl = smem;                                                    // [64*NG][WS]
+    uint32_t *Ol = reinterpret_cast<uint32_t *>(smem + 64 * NG * WS);            // [2][256][BW]
+    int *Tl = reinterpret_cast<int *>(smem + 64 * NG * WS + 2 * 256 * BW * 4);   // [64*NG] start values
+    unsigned char *Pl = reinterpret_cast<unsigned char *>(Tl + 64 * NG);         // [2][front + cap] patches
+    const int pbuf = g.front + g.cap;
+    unsigned char *Vl = Pl + 2 * pbuf;                                           // 32 bytes of pad value
+    unsigned *Ml = reinterpret_cast<unsigned *>(Vl + 32);                        // [wo][4 * U16] byte masks
+
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int l32 = lane & 31, half = lane >> 5;
+    const int o_blk = (int)blockIdx.y * 64 * NG;
+    const int UB = g.win ? 64 : 256;
+
+    struct Tile { int img, u; };                         // first image, first unit inside it
+    auto unit_row = [&](int rem) { return div_by(rem, g.ww, g.mg_ww) << g.win; };
+    // first byte of a tile's patch (a multiple of 16), and where the first output row's first input row
+    // lies relative to it (negative above the first image)
+    auto patch_start = [&](const Tile &c, int &rel) {
+        const int64_t row = (int64_t)c.img * g.h + unit_row(c.u) - g.pad;
+        const int64_t at = row * g.rowb, s = at < 0 ? 0 : at & ~(int64_t)15;
+        rel = (int)(at - s);
+        return s;
+    };
+    auto fetch = [&](const Tile &c, int buf) {
+        int rel;
+        const int64_t s0 = patch_start(c, rel);
+        const int il = div_by(c.u + UB - 1, g.upi, g.mg_upi);
+        const int last = il * g.h + unit_row(c.u + UB - 1 - il * g.upi) + g.win - unit_row(c.u) + g.kh;   // rows
+        const int64_t left = g.total - s0;
+        const int len = rel + last * g.rowb;                                  // <= cap
+        // (rounded up to whole dwords: the last valid byte's dword must not be refused)
+        const v4i rsrc = make_raw_rsrc(in + s0, (unsigned)((left < len ? left : (int64_t)len) + 3) & ~3u);
+        const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)(Pl + buf * pbuf + g.front);
+        for (int b0 = wave * 256; b0 < len; b0 += 1024) lds_dma4(rsrc, dst + b0, (unsigned)(b0 + lane * 4));
+    };
+    Tile cur, prev, next;
+    next.img = div_by((int)blockIdx.x * UB, g.upi, g.mg_upi);
+    next.u = (int)blockIdx.x * UB - next.img * g.upi;
+    prev = cur = next;
+    if ((int)blockIdx.x < g.n_tiles) fetch(next, 0);
+
+    // ---- weights of this block's channels: one thread per (channel, unit), five dwords around the
+    // unaligned start of the unit's bytes; channels past c_out address past the end and read zeros
+    constexpr int NPAIR = 64 * NG * NU, NR = (NPAIR + 255) / 256;
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(wt), 0, (g.c_out * g.kh * g.sl + 3) & ~3, 0x00020000);
+    unsigned wv[NR][5];
+    int wbase[NR], wcount[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int pair = t + 256 * r;
+        const int row = pair / NU, k16 = pair - row * NU;
+        const int ti = k16 / U16, off = (k16 - ti * U16) * 16;
+        const int left = pair < NPAIR && ti < g.kh && o_blk + row < g.c_out ? g.sl - off : 0;
+        wcount[r] = left < 0 ? 0 : (left > 16 ? 16 : left);
+        wbase[r] = wcount[r] ? ((o_blk + row) * g.kh + ti) * g.sl + off : 0x7ffffff0;
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+            wv[r][q] = __builtin_amdgcn_raw_buffer_load_b32(wr, wcount[r] ? (wbase[r] & ~3) + 4 * q : 0x7ffffff0, 0, 0);
+    }
+    int thr_t = 0;
+    if (ep.packed && t < 64 * NG && o_blk + t < g.c_out) thr_t = ep.thr[o_blk + t];
+    StepWords<TN> sw[NG];
+    if (ep.packed) {
+#pragma unroll
+        for (int grp = 0; grp < NG; ++grp) sw[grp] = load_step_words<TN>(ep, o_blk + grp * 64, l32, g.c_out);
+    }
+    const unsigned padv4 = (unsigned)(uint8_t)(int8_t)g.pad_value * 0x01010101u;
+    if (t < 8) reinterpret_cast<unsigned *>(Vl)[t] = padv4;
+    // bytes of a kernel row that lie left or right of the image, by output column
+    for (int e = t; e < g.wo * 4 * U16; e += 256) {
+        const int x = e / (4 * U16), d = e - x * (4 * U16);
+        const int lo = (g.pad - x > 0 ? g.pad - x : 0) * g.c_in;
+        const int right = g.w + g.pad - x;
+        const int hi = (right < g.kw ? (right > 0 ? right : 0) : g.kw) * g.c_in;
+        Ml[e] = bytes_below(lo - 4 * d) | ~bytes_below(hi - 4 * d);
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int pair = t + 256 * r;
+        const int row = pair / NU, k16 = pair - row * NU;
+        const unsigned sh = (unsigned)wbase[r] & 3u;
+        unsigned wd[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            wd[k] = __builtin_amdgcn_alignbyte(wv[r][k + 1], wv[r][k], sh) & bytes_below(wcount[r] - 4 * k);
+        if (pair < NPAIR) *reinterpret_cast<uint4 *>(Wl + row * WS + k16 * 16) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+    }
+    if (t < 64 * NG) {
+        int v = 0;
+        if (ep.packed && o_blk + t < g.c_out) {
+            const int bound = 1 << 30;
+            v = thr_t > bound ? bound : (thr_t < -bound ? -bound : thr_t);
+            v = -v - 1;
+        }
+        Tl[t] = v;
+    }
+    const unsigned char *wlane = Wl + l32 * WS + half * 16;     // this lane's bytes of a weight row tile
+    // 16 consecutive bytes at any LDS byte address
+    auto gather = [&](unsigned addr, const uint4 &m) {
+        const unsigned *q = reinterpret_cast<const unsigned *>(smem + (addr & ~3u));
+        const unsigned w0 = q[0], w1 = q[1], w2 = q[2], w3 = q[3], w4 = q[4];
+        const unsigned b0 = __builtin_amdgcn_alignbyte(w1, w0, addr), b1 = __builtin_amdgcn_alignbyte(w2, w1, addr);
+        const unsigned b2 = __builtin_amdgcn_alignbyte(w3, w2, addr), b3 = __builtin_amdgcn_alignbyte(w4, w3, addr);
+        return v4i{(int)((b0 & ~m.x) | (padv4 & m.x)), (int)((b1 & ~m.y) | (padv4 & m.y)),
+                   (int)((b2 & ~m.z) | (padv4 & m.z)), (int)((b3 & ~m.w) | (padv4 & m.w))};
+    };
+    auto copy_out = [&](const uint32_t *tile, const Tile &c) {
+        const int cwo = (g.c_out + 31) >> 5;
+        const int64_t left = (int64_t)(g.n - c.img) * g.upi - c.u;            // units from the tile's first
+        if (t < UB && t < left)
+            copy_words<BW>(tile + t * BW, ep.packed + ((int64_t)c.img * g.upi + c.u + t) * cwo + (o_blk >> 5), cwo,
+                           o_blk >> 5);
+    };
+
+    int it = 0;
+    for (int tile = blockIdx.x; tile < g.n_tiles; tile += (int)gridDim.x, ++it) {
+        uint32_t *Oc = Ol + (it & 1) * (256 * BW);
+        prev = cur;
+        cur = next;
+        next.u += g.step_u;
+        next.img += g.step_img;
+        if (next.u >= g.upi) { next.u -= g.upi; ++next.img; }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this tile's patch has landed
+        __syncthreads();                                      // ... for every wave; the previous tile's is consumed
+        if (tile + (int)gridDim.x < g.n_tiles) fetch(next, (it + 1) & 1);
+        if (ep.packed && it > 0) copy_out(Ol + ((it - 1) & 1) * (256 * BW), prev);
+        int rel;
+        (void)patch_start(cur, rel);
+        const int y0 = unit_row(cur.u);
+        const int pbase = (int)(Pl - smem) + (it & 1) * pbuf + g.front + rel;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row0 = wave * 64 + i * 32;
+            const int p = row0 + l32;
+            const int u = cur.u + (g.win ? p >> 2 : p);
+            const int il = div_by(u, g.upi, g.mg_upi), rem = u - il * g.upi;
+            const int ry = div_by(rem, g.ww, g.mg_ww), rx = rem - ry * g.ww;
+            const int y = g.win ? 2 * ry + ((p >> 1) & 1) : ry, x = g.win ? 2 * rx + (p & 1) : rx;
+            const int first = pbase + (il * g.h + y - y0) * g.rowb + (x - g.pad) * g.c_in;   // kernel row 0
+            // (U16 == 2: this half's unit of a row)
+            const uint4 mask = *reinterpret_cast<const uint4 *>(Ml + (U16 == 1 ? x : 2 * x + half) * 4);
+            v4i a[NS];
+#pragma unroll
+            for (int ks = 0; ks < NS; ++ks) {
+                if (U16 == 1) {
+                    const int ti = 2 * ks + half;
+                    const bool ok = (unsigned)(y - g.pad + ti) < (unsigned)g.h && ti < g.kh;
+                    a[ks] = gather((unsigned)(ok ? first + ti * g.rowb : (int)(Vl - smem)), mask);
+                } else {
+                    // unit 2 ks + half of a row of two units: kernel row ks, its lower or upper 16 bytes
+                    const bool ok = (unsigned)(y - g.pad + ks) < (unsigned)g.h && ks < g.kh;
+                    a[ks] = gather((unsigned)(ok ? first + ks * g.rowb + half * 16 : (int)(Vl - smem)), mask);
+                }
+            }
+#pragma unroll
+            for (int cg = 0; cg < NG; ++cg) {
+                __builtin_amdgcn_s_setprio(1);           // multiplies outrank other waves' epilogues
+                const int *Tg = Tl + cg * 64;
+                v16i acc[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[j] = load_bias16<v16i>(Tg + j * 32, half);
+#pragma unroll
+                for (int ks = 0; ks < NS; ++ks)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const v4i b = *reinterpret_cast<const v4i *>(wlane + (cg * TN + j) * 32 * WS + ks * 32);
+                        acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b, a[ks], acc[j], 0, 0, 0);   // rows = channels
+                    }
+                __builtin_amdgcn_s_setprio(0);
+                const int ch0 = o_blk + cg * 64;
+                if (ep.preact) {
+                    auto getx = [&](int, int j, int r) {
+                        return acc[j][r] - Tg[j * 32 + (r >> 2) * 8 + half * 4 + (r & 3)];
+                    };
+                    auto getpix = [&](int) -> int64_t {
+                        if (u >= (int64_t)(g.n - cur.img) * g.upi) return -1;
+                        return ((int64_t)(cur.img + il) * (g.upi / g.ww << g.win) + y) * g.wo + x;
+                    };
+                    conv_store_preact<1, TN>(getx, getpix, ch0, half, g.c_out, ep.preact);
+                }
+                if (ep.packed) {
+                    StepWords<TN> cursw = sw[0];
+#pragma unroll
+                    for (int q = 1; q < NG; ++q)
+                        if (cg == q) cursw = sw[q];
+                    auto gets = [&](int, int j, int r) { return acc[j][r]; };
+                    conv_tile_step_to_lds<1, TN>(gets, row0, cg * TN, BW, l32, half, cursw, ep.pool,
+                                                 ep.pool_first != 0, Oc);
+                }
+                __builtin_amdgcn_sched_barrier(0);      // one group's registers at a time
+            }
+        }
+    }
+    if (ep.packed && it > 0) {
+        __syncthreads();
+        copy_out(Ol + ((it - 1) & 1) * (256 * BW), cur);
+    }
+}
+
 // 1x1, pad 0, c_in % 16 == 0: int8 GEMM  X[m][o] = sum_c A[m][c] * W[o][c];  m = pixel index.
 // Block = 2 x 2 waves, one 32 x 32 tile each; operands are 16-byte global loads.
 __global__ __launch_bounds__(256) void fc_first_mfma(const int8_t *__restrict__ A, const int8_t *__restrict__ Wt,
@@ -892,11 +1135,6 @@ struct FirstGeomS {
     int w2, hw2;                 // output columns and pixels per image, in windows when pooling
     unsigned mg_w2, mg_hw2;
 };
-
-__device__ __forceinline__ unsigned bytes_below(int t)      // mask of the bytes b < t of a dword
-{
-    return t <= 0 ? 0u : (t >= 4 ? 0xffffffffu : (1u << (8 * t)) - 1u);
-}
 
 __global__ __launch_bounds__(64) void conv_first_small(const int8_t *__restrict__ in, const int8_t *__restrict__ wt,
                                                        FirstGeomS g, EpiArgs ep, ClearArgs clr)
@@ -1143,6 +1381,65 @@ bnn_status launch_first_img(const int8_t *in, const int8_t *wt, int n, int h, in
     return hip_result(hipGetLastError());
 }
 
+// Raster-order tiles: kernel rows of at most 32 bytes and at most 14 16-byte units in all, patches of
+// at most 8 KB, and less padding than the kernel is high (the input rows of consecutive output rows
+// then never run backwards from one image to the next).  BNN_ERR_UNSUPPORTED otherwise.
+template <int NG>
+bnn_status launch_first_lin(const int8_t *in, const int8_t *wt, int n, int h, int w, int c_in, int c_out, int kh,
+                            int kw, int pad, int pad_value, const EpiArgs &ep, const ClearArgs &clr, hipStream_t s)
+{
+    FirstGeomL g;
+    g.n = n; g.h = h; g.w = w; g.c_in = c_in; g.c_out = c_out; g.kh = kh; g.kw = kw;
+    g.pad = pad; g.pad_value = pad_value;
+    const int ho = h + 2 * pad - kh + 1;
+    g.wo = w + 2 * pad - kw + 1;
+    g.sl = kw * c_in; g.rowb = w * c_in;
+    g.total = (int64_t)n * h * w * c_in;
+    const int u16 = (g.sl + 15) / 16, ns = (kh * u16 + 1) / 2;
+    if (u16 > 2 || ns > 7 || ho > 1024 || g.wo > 256 || pad >= kh || (int64_t)c_out * kh * g.sl > 0x7ffffff0LL)
+        return BNN_ERR_UNSUPPORTED;
+    g.win = ep.packed && ep.pool == 2 ? 1 : 0;
+    g.upi = (ho >> g.win) * (g.wo >> g.win);
+    g.ww = g.wo >> g.win;
+    const int ub = 256 >> (2 * g.win);
+    const int64_t tiles = ((int64_t)n * g.upi + ub - 1) / ub;
+    // rows of units that a tile can touch; from one image to the next the input rows advance by h, the
+    // output rows by ho
+    const int urows = (ub - 1 + g.ww - 1) / g.ww + 1, cross = (ub - 1 + g.upi - 1) / g.upi;
+    const int64_t rows = (int64_t)(urows << g.win) + kh + (int64_t)cross * (h > ho ? h - ho : 0);
+    const int64_t bytes = rows * g.rowb + 16;
+    if (tiles > 0x3fffffffLL || bytes > 8192) return BNN_ERR_UNSUPPORTED;
+    g.n_tiles = (int)tiles;
+    g.front = (pad * c_in + 15) & ~15;
+    // slack: gathers read whole units, up to the padding's bytes past a row's end
+    g.cap = (int)((bytes + 64 + pad * c_in + 255) & ~(int64_t)255);
+    g.mg_upi = magic_floor(g.upi);
+    g.mg_ww = magic_floor(g.ww);
+    const int n_co_tiles = (c_out + 64 * NG - 1) / (64 * NG);
+    const int nsx = u16 == 2 ? (ns <= 3 ? 3 : (ns <= 5 ? 5 : 7)) : ns;
+    if (n_co_tiles > 65535 || (u16 == 1 && ns > 4)) return BNN_ERR_UNSUPPORTED;
+    const size_t smem = (size_t)64 * NG * (nsx * 32 + 16) + 2 * 256 * 2 * NG * 4 + 64 * NG * 4 +
+                        2 * (size_t)(g.front + g.cap) + 32 + (size_t)g.wo * 16 * u16;
+    if (smem > 64 * 1024) return BNN_ERR_UNSUPPORTED;
+    const int bx = (int)(tiles < 1024 ? tiles : 1024);
+    g.step_img = (int)((int64_t)bx * ub / g.upi);
+    g.step_u = (int)((int64_t)bx * ub - (int64_t)g.step_img * g.upi);
+    const dim3 grid((unsigned)bx, (unsigned)n_co_tiles);
+#define BNN_FIRST_LIN(NS, U) hipLaunchKernelGGL((conv_first_lin<NG, NS, U>), grid, dim3(256), smem, s, in, wt, g, ep, clr)
+    if (u16 == 1) {
+        if (ns == 1) BNN_FIRST_LIN(1, 1);
+        else if (ns == 2) BNN_FIRST_LIN(2, 1);
+        else if (ns == 3) BNN_FIRST_LIN(3, 1);
+        else BNN_FIRST_LIN(4, 1);
+    } else {
+        if (nsx == 3) BNN_FIRST_LIN(3, 2);
+        else if (nsx == 5) BNN_FIRST_LIN(5, 2);
+        else BNN_FIRST_LIN(7, 2);
+    }
+#undef BNN_FIRST_LIN
+    return hip_result(hipGetLastError());
+}
+
 }  // namespace
 
 bnn_status launch_conv_first_int8(const int8_t *in, int n, int h, int w, int c_in, const int8_t *wt,
@@ -1179,6 +1476,20 @@ bnn_status launch_conv_first_int8(const int8_t *in, int n, int h, int w, int c_i
         const bool two_groups = c_out > 64 && ptiles * ((c_out + 127) / 128) >= 256;
         const bnn_status st = two_groups ? launch_first_img<2>(in, wt, n, h, w, c_in, c_out, pad_value, ep, clr, s)
                                          : launch_first_img<1>(in, wt, n, h, w, c_in, c_out, pad_value, ep, clr, s);
+        if (st != BNN_ERR_UNSUPPORTED) return st;
+    }
+    // Any image size, kernel rows of at most 32 bytes: tiles in raster order.  Images that fill their
+    // rectangles stay with the next kernel where it has fixed operand addresses (kernel rows of 16 bytes,
+    // at most four) and at most 64 channels over which to spread the raster tiles' address arithmetic:
+    // 665 x 48 x 48 x 3 -> 47 with pooling 19.6 us there and 21.4 here; 300 x 64 x 64 x 3 -> 128 25.8 and 24.7.
+    const TileShape rect = make_tile_shape(ho_, wo_, 256);
+    const int64_t rect_tiles = (int64_t)rect.tiles_x * rect.tiles_y * ((n + rect.ni - 1) / rect.ni);
+    const int64_t ptiles = ((int64_t)n * ho_ * wo_ + 255) / 256;
+    if (!(rect_tiles * 20 <= ptiles * 21 && c_out <= 64 && kw * c_in <= 16 && kh <= 4)) {
+        const bool two_groups = c_out > 64 && ptiles * ((c_out + 127) / 128) >= 256;
+        const bnn_status st =
+            two_groups ? launch_first_lin<2>(in, wt, n, h, w, c_in, c_out, kh, kw, pad, pad_value, ep, clr, s)
+                       : launch_first_lin<1>(in, wt, n, h, w, c_in, c_out, kh, kw, pad, pad_value, ep, clr, s);
         if (st != BNN_ERR_UNSUPPORTED) return st;
     }
     // small kernels: patch + weights in LDS, matrix cores

@@ -292,6 +292,44 @@ def test_conv_binary_closed_form_borders():
     assert r[0, h - 1, w - 1, co - 1] == -c
 
 
+# First layers over images of any size: tiles in raster order.  Kernel rows of one and two 16-byte
+# units, one to seven kernel rows, paddings up to the kernel height less one (and one beyond, which
+# another kernel takes), tiles inside a row, over many images and past the last one, more tiles than
+# blocks, tensors that are no whole number of dwords.
+@pytest.mark.parametrize("n,h,w,ci,co,kh,kw,pad,padv", [
+    (500, 30, 30, 3, 100, 3, 3, 1, -1), (90, 41, 37, 1, 39, 3, 3, 1, 7), (937, 18, 18, 3, 70, 5, 5, 2, -1),
+    (60, 50, 50, 4, 128, 5, 5, 2, -128), (40, 35, 33, 3, 66, 7, 7, 3, 127), (700, 9, 11, 4, 33, 8, 4, 0, 0),
+    (900, 11, 13, 3, 40, 4, 5, 3, 5), (50, 40, 200, 3, 65, 3, 3, 1, -1), (301, 22, 22, 5, 129, 3, 3, 2, -1),
+    (120, 33, 31, 7, 64, 1, 4, 0, 3), (800, 10, 10, 6, 96, 2, 5, 2, -1), (4001, 9, 9, 1, 31, 3, 3, 1, -1)])
+def test_conv_first_raster_tiles(n, h, w, ci, co, kh, kw, pad, padv):
+    print("first raster", n, h, w, ci, co, kh, kw, pad, padv, flush=True)
+    rng = rng_of(n + 3 * h + 5 * w + 7 * ci + 11 * co + kh)
+    x = rng.integers(-128, 128, size=(n, h, w, ci), dtype=np.int8)
+    wt = pm1(rng, (co, kh, kw, ci))
+    want = oracle.conv2d(x, wt, pad, padv)
+    ho, wo = want.shape[1:3]
+    xd, wd = dev(x), dev(wt)
+    raw = fill_i32((n + 1, ho, wo, co), 4242)
+    P.bnn_conv_first_int8(xd, n, h, w, ci, wd, co, kh, kw, pad, padv, preact_out=raw)
+    np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
+    assert int((raw[n] != 4242).sum()) == 0
+    thr = want[n // 2, ho // 2, wo // 2].copy()                # ties
+    thr[::2] = rng.integers(-500, 501, size=thr[::2].size)
+    flip = rng.integers(0, 2, size=co).astype(np.uint8)
+    s = oracle.step(want, thr, flip)
+    forms = [(1, 0, s)]
+    if ho % 2 == 0 and wo % 2 == 0:
+        forms += [(2, 0, oracle.maxpool2(s)), (2, 1, oracle.step(oracle.maxpool2(want), thr, flip))]
+    for pool, pool_first, ref in forms:
+        pk = fill_i32((n + 1, ho // pool, wo // pool, (co + 31) // 32), -1)
+        raw.fill_(4242)
+        P.bnn_conv_first_int8(xd, n, h, w, ci, wd, co, kh, kw, pad, padv, thr=dev(thr), flip=dev(flip), pool=pool,
+                              pool_first=pool_first, preact_out=raw, packed_out=pk)
+        np.testing.assert_array_equal(host_u32(pk[:n]), pack_pm1(ref), err_msg=f"pool {pool} {pool_first}")
+        assert int((pk[n] != -1).sum()) == 0
+        np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
+
+
 # Images whose sizes leave rectangular pixel tiles half empty, in batches large enough for the tile
 # kernels to take tiles in raster order instead: every channel width, resident and streamed weights,
 # the three block tiles, windows and pixels, tiles that span many images or part of a row.
