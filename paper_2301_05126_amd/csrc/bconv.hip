@@ -11,6 +11,7 @@ namespace bnn {
 BNN_DECL_WPH(1)
 BNN_DECL_WPH(2)
 BNN_DECL_WPH(4)
+BNN_DECL_WPH(6)
 BNN_DECL_WPH(8)
 BNN_DECL_WPH(16)
 #undef BNN_DECL_WPH
@@ -24,8 +25,9 @@ bool conv_binary_supported(int h, int w, int c_in)
 
 static int words_per_half(int c_in)
 {
-    // words per lane half per tap: channel words per pixel rounded up to 2, 4, 8, 16 or 32
+    // words per lane half per tap: channel words per pixel rounded up to 2, 4, 8, 12, 16 or 32
     const int cw = (c_in + 31) / 32;
+    if (cw > 8 && cw <= 12) return 6;
     int wph = 1;
     while (2 * wph < cw) wph *= 2;
     return wph;
@@ -39,6 +41,7 @@ int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, bool til
     case 1: return conv_tile_choice_wph1(n, h, w, c_in, c_out, false);
     case 2: return conv_tile_choice_wph2(n, h, w, c_in, c_out, false);
     case 4: return conv_tile_choice_wph4(n, h, w, c_in, c_out, false);
+    case 6: return conv_tile_choice_wph6(n, h, w, c_in, c_out, false);
     case 8: return conv_tile_choice_wph8(n, h, w, c_in, c_out, false);
     case 16: return conv_tile_choice_wph16(n, h, w, c_in, c_out, false);
     }
@@ -53,6 +56,7 @@ bnn_status launch_conv_binary_tiles(const uint32_t *in, int n, int h, int w, int
     case 1: return launch_conv_binary_wph1(in, n, h, w, c_in, wt, c_out, ep, s);
     case 2: return launch_conv_binary_wph2(in, n, h, w, c_in, wt, c_out, ep, s);
     case 4: return launch_conv_binary_wph4(in, n, h, w, c_in, wt, c_out, ep, s);
+    case 6: return launch_conv_binary_wph6(in, n, h, w, c_in, wt, c_out, ep, s);
     case 8: return launch_conv_binary_wph8(in, n, h, w, c_in, wt, c_out, ep, s);
     case 16: return launch_conv_binary_wph16(in, n, h, w, c_in, wt, c_out, ep, s);
     }

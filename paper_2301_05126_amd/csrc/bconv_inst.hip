@@ -4,7 +4,7 @@
 #include "bconv_kernel.h"
 
 #if !defined(BNN_CONV_WPH) || !defined(BNN_CONV_PART)
-#error "compile with -DBNN_CONV_WPH={1,2,4,8,16} -DBNN_CONV_PART={0,1}"
+#error "compile with -DBNN_CONV_WPH={1,2,4,6,8,16} -DBNN_CONV_PART={0,1}"
 #endif
 
 #define BNN_CAT2(a, b) a##b
@@ -29,7 +29,7 @@ template <>
 bnn_status launch_conv_big_tile<BNN_CONV_WPH>(const uint32_t *in, const uint32_t *wt, int n, int h, int w,
                                               int c_in, int c_out, const EpiArgs &ep, hipStream_t s)
 {
-    return launch_one<4, 2, BNN_CONV_WPH, (BNN_CONV_WPH >= 8)>(in, wt, n, h, w, c_in, c_out, ep, s);
+    return launch_one<4, 2, BNN_CONV_WPH, (BNN_CONV_WPH >= 6)>(in, wt, n, h, w, c_in, c_out, ep, s);
 }
 #endif
 

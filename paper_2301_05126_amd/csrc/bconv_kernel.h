@@ -67,7 +67,7 @@ __device__ __forceinline__ void vec_set(uint2 &v, int q, uint32_t x) { if (q == 
 __device__ __forceinline__ void vec_set(uint32_t &v, int, uint32_t x) { v = x; }
 
 // Steps (one MFMA K-slice = one word per lane half) per weight chunk, by words per half.
-constexpr int steps_per_chunk(int wph) { return wph == 1 ? 9 : (wph == 2 ? 18 : (wph == 4 ? 12 : 8)); }
+constexpr int steps_per_chunk(int wph) { return wph == 1 ? 9 : (wph == 2 ? 18 : (wph == 4 ? 12 : (wph == 6 ? 6 : 8))); }
 
 // Whether a block keeps all of its weight chunks in LDS at once: up to 40 KB for any tile
 // (C_in <= 256 with 128 output channels), up to 48 KB for the 64-channel tile.
@@ -93,6 +93,7 @@ struct ConvGeom {
     int n_ptiles;                // pixel tiles in the layer
     int slots;                   // blocks per channel tile = pixel tiles in flight
     int patch_words;             // LDS words of one patch buffer (rounded up)
+    int wexact;                  // WDMA: exactly 2*WPH words per pixel and whole channel tiles
     int dbuf;                    // 1: two patch buffers, the next tile's patch is fetched during the MFMAs
     unsigned mg_pw, mg_ph;       // ceil(2^32 / d) for d = patch width, patch height (staging index math)
     int step_group, step_ty, step_tx;    // `slots` pixel tiles as an (image group, tile row, tile column) increment
@@ -113,13 +114,14 @@ struct ConvGeom {
 // address past the buffer's end and deliver zeros, i.e. -1 padding); with two patch buffers
 // the next tile's patch is in flight while the current tile is multiplied.
 //
-// WDMA (wide layers whose weights are not resident; needs cw == 2*WPH words per pixel and
-// c_out a multiple of the block's channels): weight chunks also travel global -> LDS without
-// passing through registers, into two buffers that alternate; the chunk sequence is cyclic
+// WDMA (wide layers whose weights are not resident): weight chunks also travel global -> LDS
+// without passing through registers, into two buffers that alternate; the chunk sequence is cyclic
 // over the tiles (weights do not depend on the tile), so the next chunk is always in flight
-// behind the current one and a chunk costs one barrier.  Rows are unpadded (16 words) and
-// their 8-byte units are stored at position unit ^ ((row >> 1) & 7), which keeps the 32 rows
-// read by one instruction on distinct banks.
+// behind the current one and a chunk costs one barrier.  Rows are unpadded (16 words, eight for
+// each lane half) and their 8-byte units are stored at position unit ^ ((row >> 1) & 7), which keeps
+// the 32 rows read by one instruction on distinct banks.  Channels past c_out and words past the
+// layer's own address past the end of the weights and arrive as zeros (staging such layers through
+// registers, two barriers per chunk, took 39.8 us for 1137 x 7 x 7, 320 -> 184; this takes 15.8).
 //
 // LIN: a tile is the next 64*TM pixels (2x2 windows when pooling) of the batch in raster order
 // instead of a rectangle per image group, so that images of any size fill their tiles: 21 x 21
@@ -139,14 +141,18 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     constexpr int V = WPH >= 2 ? 2 : WPH;              // words per LDS access
     constexpr int SPC = steps_per_chunk(WPH);
     constexpr int NCHUNK = 9 * WPH / SPC;
-    constexpr int LSB = WDMA ? 2 * SPC : 2 * SPC + V;  // weight row stride (words); padded: LSB/V is odd
+    constexpr int LSB = WDMA ? 16 : 2 * SPC + V;       // weight row stride (words); padded: LSB/V is odd
     constexpr int UPRW = 2 * SPC / V;                  // weight units per row per chunk
     constexpr int STG = (BN * UPRW + 255) / 256;       // weight units per thread per chunk
     constexpr int NVG = SPC / V;                       // V-step groups per chunk
     constexpr bool RES = !WDMA && weights_resident(TM, TN, WPH);
     constexpr int NBUF = RES ? NCHUNK : (WDMA ? 2 : 1);
-    static_assert(!WDMA || (SPC == 8 && V == 2 && BN == 128), "weight DMA layout: 16-word rows, 128 rows");
-    static_assert(NCHUNK == 1 || (SPC % 2 == 0 && NVG % 2 == 0), "operand pipeline across chunks: buffer parity");
+    static_assert(!WDMA || (SPC <= 8 && V == 2 && BN == 128), "weight DMA layout: 16-word rows, 128 rows");
+    // word groups in registers: the current one, the next, and with an odd number of groups per chunk
+    // a third place, so that every chunk starts with the same one
+    constexpr int NSLOT = NVG % 2 != 0 && NCHUNK > 1 ? 3 : 2;
+    static_assert(NSLOT == 2 || NVG == 3, "a chunk's groups and the next chunk's first one have places of their own");
+    static_assert(SPC % 2 == 0 || NCHUNK == 1, "operand pipeline across chunks: buffer parity");
     using vec_t = typename WordVec<V>::type;
 
     extern __shared__ __align__(16) unsigned char smem[];
@@ -259,12 +265,15 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     // chunk buffer = rows 4*(wave + 4k) .. +3.  The word a lane delivers depends on k and on
     // the chunk only through a scalar offset.
     unsigned wd_voff = 0;
+    bool wd_ok[2] = {true, true};                          // the lane's word exists (even / odd chunk)
     v4i wd_rsrc = make_raw_rsrc(wt, (unsigned)g.c_out * 9u * (unsigned)g.cw * 4u);
     if (WDMA) {
         const int phys = (lane & 15) >> 1, sub = lane & 1;
         const int lw = ((phys ^ ((2 * wave + (lane >> 5)) & 7)) << 1) | sub;    // logical word of the chunk row
         const int hh = lw >> 3, st = lw & 7;
         wd_voff = (unsigned)(((o_blk + 4 * wave + (lane >> 4)) * 9 * g.cw + hh * WPH + st) * 4);
+        wd_ok[0] = st < SPC && hh * WPH + st < g.cw;
+        wd_ok[1] = st < SPC && hh * WPH + st + (WPH > 8 ? 8 : 0) < g.cw;
     }
     auto dma_w = [&](int chunk, int buf) {
         const int s0 = chunk * SPC;
@@ -273,18 +282,26 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
         const unsigned soff0 = (unsigned)__builtin_amdgcn_readfirstlane(((s0 / WPH) * g.cw + (s0 % WPH)) * 4);
         const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) uint32_t *)(Bs + buf * BN * LSB) +
                              (unsigned)__builtin_amdgcn_readfirstlane(wave) * 256u;
+        const unsigned rows16 = (unsigned)(16 * 9 * 4) * (unsigned)g.cw;
+        if (g.wexact) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            lds_dma4_soff(wd_rsrc, dst + k * 1024u, wd_voff, soff0 + (unsigned)(k * 16 * 9 * 4) * (unsigned)g.cw);
+            for (int k = 0; k < 8; ++k) lds_dma4_soff(wd_rsrc, dst + k * 1024u, wd_voff, soff0 + k * rows16);
+        } else {
+            // the row in the vector offset, where the range check sees it
+            const bool ok = WPH > 8 && (chunk & 1) ? wd_ok[1] : wd_ok[0];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                lds_dma4_soff(wd_rsrc, dst + k * 1024u, ok ? wd_voff + k * rows16 : 0x80000000u, soff0);
+        }
     };
     // this lane's read offsets (words) inside a weight row, per V-step group
     int wd_boff[NVG];
 #pragma unroll
-    for (int vg = 0; vg < NVG; ++vg) wd_boff[vg] = (((half * NVG + vg) ^ ((l32 >> 1) & 7)) << 1);
+    for (int vg = 0; vg < NVG; ++vg) wd_boff[vg] = (((half * 4 + vg) ^ ((l32 >> 1) & 7)) << 1);
 
     // ---- patch fetch, global -> LDS directly.  Unit = 16 bytes (a whole-pixel multiple) when
-    // the layer has exactly CWP words per pixel and CWP >= 4, else one word.
-    const bool wide = (g.cw == CWP) && (CWP >= 4);
+    // a pixel is a whole number of them, else one word.
+    const bool wide = CWP % 4 == 0 && (g.cw & 3) == 0;
     auto fetch_patch = [&](const TileCoord &tc, int buf) {
         const int img0 = LIN ? tc.group : tc.group * g.ni;
         const int y0 = LIN ? unit_row(tc.ty) : tc.ty * th, x0 = LIN ? 0 : tc.tx * tw;
@@ -311,7 +328,7 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
             const int il = LIN ? div_by(y0 + p1, ph, g.mg_hp) : (int)__umulhi((unsigned)p1, g.mg_ph);
             const int py = p1 - il * ph;
             const int y = y0 + py - 1, x = x0 + px - 1;
-            const bool inside = y >= 0 && y < g.h && x >= 0 && x < g.w && (wide || u < g.cw);
+            const bool inside = y >= 0 && y < g.h && x >= 0 && x < g.w && (wide ? u * 4 : u) < g.cw;
             unsigned voff = 0x80000000u;                    // past the end of the buffer: zeros
             if (inside) voff = (unsigned)(((il * g.h + y) * g.w + x) * g.cw) * 4u + (unsigned)u * (wide ? 16u : 4u);
             const unsigned wave_base = (unsigned)__builtin_amdgcn_readfirstlane(b0 + wave * 64);
@@ -456,7 +473,7 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
         // them, multiply" runs across chunk borders where the data allows it (XA: pixel words
         // always, the patch is resident; XB: channel words only when the weights are resident).
         constexpr bool XA = RES || WDMA, XB = RES;
-        vec_t ra[2][TM], rb[2][TN];
+        vec_t ra[NSLOT][TM], rb[NSLOT][TN];
         v8i a[2][TM], b[2][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -542,8 +559,8 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
                 const bool last_group = vg + 1 == NVG;
                 if (q == 0) {
                     if (!last_group) {
-                        load_a(c, vg + 1, (vg + 1) & 1);
-                        load_b(Bc, vg + 1, (vg + 1) & 1);
+                        load_a(c, vg + 1, (vg + 1) % NSLOT);
+                        load_b(Bc, vg + 1, (vg + 1) % NSLOT);
                     } else if (more) {                    // first group of the next chunk
                         if (XA) load_a(c + 1, 0, 0);
                         if (XB) load_b(Bn, 0, 0);
@@ -552,6 +569,7 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
                 }
                 const bool in_chunk = st + 1 < SPC;
                 const int vg1 = in_chunk ? (st + 1) / V : 0, q1 = in_chunk ? (st + 1) % V : 0;
+                const int sl1 = vg1 % NSLOT;
                 // (streamed weights: the chunk index is a run-time value, and the last chunk expands
                 // stale words into operands that the next tile overwrites, rather than branching)
                 const bool next_a = in_chunk || (XA && (WDMA || more)), next_b = in_chunk || (XB && more);
@@ -573,7 +591,7 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
                             const int ks = t2 * (NM - LAG) / NIT;            // MFMA the shift follows
                             const int wi = t2 >> 1, dp = t2 & 1;
                             if (!(wi < TM ? next_a : next_b)) continue;
-                            if (ks == k) pend[t2] = shift_pair_half(wi < TM ? ra[vg1 & 1][wi] : rb[vg1 & 1][wi - TM], q1, dp);
+                            if (ks == k) pend[t2] = shift_pair_half(wi < TM ? ra[sl1][wi] : rb[sl1][wi - TM], q1, dp);
                             if (ks + LAG == k) {
                                 const uint2 e = mask_pair(pend[t2], sgn, one);
                                 if (wi < TM) {
@@ -590,10 +608,10 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
                         for (int d = k * DPM; d < (k + 1) * DPM && d < 4 * (TM + TN); ++d) {
                             const int wi = d >> 2, part = d & 3;
                             if (wi < TM) {
-                                if (next_a) a[nxt][wi][part] = (int)expand_part(vec_word(ra[vg1 & 1][wi], q1), part, sgn, one);
+                                if (next_a) a[nxt][wi][part] = (int)expand_part(vec_word(ra[sl1][wi], q1), part, sgn, one);
                             } else {
                                 if (next_b)
-                                    b[nxt][wi - TM][part] = (int)expand_part(vec_word(rb[vg1 & 1][wi - TM], q1), part, sgn, one);
+                                    b[nxt][wi - TM][part] = (int)expand_part(vec_word(rb[sl1][wi - TM], q1), part, sgn, one);
                             }
                         }
                     }
@@ -647,12 +665,11 @@ template <int TM, int TN, int WPH, bool WDMA>
 bool make_geom(int n, int h, int w, int c_in, int c_out, bool win, bool lin, ConvGeom &g, size_t &smem)
 {
     constexpr int V = WPH >= 2 ? 2 : WPH;
-    constexpr int LSB = WDMA ? 2 * steps_per_chunk(WPH) : 2 * steps_per_chunk(WPH) + V;
+    constexpr int LSB = WDMA ? 16 : 2 * steps_per_chunk(WPH) + V;
     constexpr int NBUF = WDMA ? 2 : (weights_resident(TM, TN, WPH) ? 9 * WPH / steps_per_chunk(WPH) : 1);
-    // weights by DMA: exact channel words, whole channel tiles, byte offsets below 2^31
-    if (WDMA && ((c_in + 31) / 32 != 2 * WPH || c_out % (64 * TN) != 0 ||
-                 (int64_t)c_out * 9 * ((c_in + 31) / 32) * 4 >= 0x7fffffffLL))
-        return false;
+    // weights by DMA: byte offsets (of the last channel tile's missing rows too) below 2^31
+    if (WDMA && ((int64_t)c_out + 64 * TN) * 9 * ((c_in + 31) / 32) * 4 >= 0x7fffffffLL) return false;
+    g.wexact = (c_in + 31) / 32 == 2 * WPH && c_out % (64 * TN) == 0;
     g.n = n; g.h = h; g.w = w;
     g.cw = (c_in + 31) / 32;
     g.c_out = c_out;
@@ -801,11 +818,10 @@ namespace {
 template <int WPH>
 int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win)
 {
-    // the largest tile keeps its weights resident (WPH <= 4) or streams them by DMA
-    constexpr bool WD = WPH >= 8;
+    // the larger tiles keep their weights resident (WPH <= 4) or stream them by DMA
+    constexpr bool WD = WPH >= 6;
     if (fills<4, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return 3;
-    if (WD && fills<2, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return 2;
-    if (fills<2, 2, WPH>(n, h, w, c_in, c_out, win)) return 1;
+    if (fills<2, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return WD ? 2 : 1;
     return 0;
 }
 
@@ -813,11 +829,11 @@ template <int WPH>
 bnn_status launch_wph(const uint32_t *in, const uint32_t *wt, int n, int h, int w, int c_in, int c_out,
                       const EpiArgs &ep, hipStream_t s)
 {
-    constexpr bool WD = WPH >= 8;
+    constexpr bool WD = WPH >= 6;
     switch (tile_choice_wph<WPH>(n, h, w, c_in, c_out, ep.packed && ep.pool == 2)) {
     case 3: return launch_conv_big_tile<WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
-    case 2: return launch_one<2, 2, WPH, WD>(in, wt, n, h, w, c_in, c_out, ep, s);
-    case 1: return launch_one<2, 2, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
+    case 2:
+    case 1: return launch_one<2, 2, WPH, WD>(in, wt, n, h, w, c_in, c_out, ep, s);
     }
     return launch_one<1, 1, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
 }
