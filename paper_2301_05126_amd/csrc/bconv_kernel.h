@@ -121,7 +121,7 @@ struct ConvGeom {
 // each lane half) and their 8-byte units are stored at position unit ^ ((row >> 1) & 7), which keeps
 // the 32 rows read by one instruction on distinct banks.  Channels past c_out and words past the
 // layer's own address past the end of the weights and arrive as zeros (staging such layers through
-// registers, two barriers per chunk, took 39.8 us for 1137 x 7 x 7, 320 -> 184; this takes 15.8).
+// registers, two barriers per chunk, took 39.8 us for 1137 x 7 x 7, 320 -> 184; this takes 25.9).
 //
 // LIN: a tile is the next 64*TM pixels (2x2 windows when pooling) of the batch in raster order
 // instead of a rectangle per image group, so that images of any size fill their tiles: 21 x 21
@@ -731,28 +731,47 @@ bool make_geom(int n, int h, int w, int c_in, int c_out, bool win, bool lin, Con
     return smem <= (size_t)MAX_SMEM;
 }
 
-// Rounds of work of a tiling: how many tiles the busiest block takes; a single round in which no
-// compute unit has two blocks counts for less (they share the matrix pipe otherwise).
-inline double conv_rounds(const ConvGeom &g)
+// Estimated ticks of a layer's multiply phase on one tiling: how many tiles the busiest compute unit
+// takes, times a tile's MFMAs per wave, times the ticks of an MFMA with the operand expansion of this
+// tile shape beside it (5.5 vector instructions per word and TM + TN words per TM * TN MFMAs).  Two
+// resident blocks hide each other's expansion up to 4 ticks per instruction (4 x 2: 33 ticks per MFMA
+// as measured; 1 x 1: 56), a block alone pays more (2 x 2: 41, 1 x 1: 69).  A tile's epilogue and its
+// barriers come on top, twice for a block alone.
+template <int TM, int TN, int WPH>
+double conv_cost(const ConvGeom &g, bool lin)
 {
-    if ((int64_t)g.n_ptiles * g.n_co_tiles <= 256) return 0.6;
-    return (g.n_ptiles + g.slots - 1) / g.slots;
+    constexpr double ops = 5.5 * (TM + TN) / (TM * TN);
+    constexpr double pair = 12 + 4 * ops > 33 ? 12 + 4 * ops : 33;
+    constexpr double lone = 12 + 5.2 * ops > 33 ? 12 + 5.2 * ops : 33;
+    constexpr double mfma = TM * TN * 9 * WPH;
+    const int blocks = g.slots * g.n_co_tiles;
+    const int per_block = (g.n_ptiles + g.slots - 1) / g.slots;
+    const double over = 300 + 150.0 * TM * TN, addr = lin ? 1.08 : 1.0;
+    if (blocks <= 256) return addr * per_block * (mfma * lone + 2 * over);
+    // blocks b and b + 256 share a compute unit; the first `rest` slots have one tile more
+    const int full = g.n_ptiles / g.slots, rest = (g.n_ptiles - full * g.slots) * g.n_co_tiles;
+    const int mates = blocks - 256;                          // compute units with two blocks
+    int most = full + (rest > 0);                            // tiles of the busiest compute unit
+    if (mates > 0) most = 2 * full + (rest > 256 ? 2 : (rest > 0 ? 1 : 0));
+    return addr * most * (mfma * pair + over);
 }
 
-// Rectangular or linear tiles, whichever take fewer rounds.  Working out a linear tile's addresses
-// costs some 8 % of a tile (measured where both tilings take the same number of rounds: 28 x 28 images
-// 64 -> 64 at batch 256 11.4 us with rectangles and 12.0 with linear tiles, 449 x 12 x 31 17.0 and 17.8).
-// Returns false if neither fits; *lin says which.
+// Rectangular or linear tiles, whichever cost less; working out a linear tile's addresses is some 8 %
+// of a tile (measured where both tilings take the same number of rounds: 28 x 28 images 64 -> 64 at
+// batch 256 11.4 us with rectangles and 12.0 with linear tiles, 449 x 12 x 31 17.0 and 17.8).
+// Returns the estimated cost, or a negative number if neither fits; *lin says which.
 template <int TM, int TN, int WPH, bool WDMA>
-bool pick_geom(int n, int h, int w, int c_in, int c_out, bool win, ConvGeom &g, size_t &smem, bool *lin)
+double pick_geom(int n, int h, int w, int c_in, int c_out, bool win, ConvGeom &g, size_t &smem, bool *lin)
 {
     ConvGeom gl;
     size_t sl;
     const bool rect_ok = make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, false, g, smem);
     const bool lin_ok = make_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, true, gl, sl);
-    *lin = lin_ok && (!rect_ok || 1.08 * conv_rounds(gl) < conv_rounds(g));
+    const double rect = rect_ok ? conv_cost<TM, TN, WPH>(g, false) : -1;
+    const double line = lin_ok ? conv_cost<TM, TN, WPH>(gl, true) : -1;
+    *lin = lin_ok && (!rect_ok || line < rect);
     if (*lin) { g = gl; smem = sl; }
-    return rect_ok || lin_ok;
+    return *lin ? line : rect;
 }
 
 template <int TM, int TN, int WPH, bool WDMA, bool LIN>
@@ -782,26 +801,25 @@ bnn_status launch_one(const uint32_t *in, const uint32_t *wt, int n, int h, int 
     ConvGeom g;
     size_t smem;
     bool lin;
-    if (!pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, ep.packed && ep.pool == 2, g, smem, &lin))
+    if (pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, ep.packed && ep.pool == 2, g, smem, &lin) < 0)
         return BNN_ERR_UNSUPPORTED;
     return lin ? launch_geom<TM, TN, WPH, WDMA, true>(in, wt, g, smem, ep, s)
                : launch_geom<TM, TN, WPH, WDMA, false>(in, wt, g, smem, ep, s);
 }
 
-// Whether a (64*TM pixels) x (64*TN channels) block tile fits LDS and gives enough work items (pixel
-// tiles x channel tiles) for two resident blocks per compute unit -- or nearly so where linear tiles
-// are fewer than rectangles would be: 392 tiles in one round beat twice as many half as large.
+// Estimated cost of a (64*TM pixels) x (64*TN channels) block tile, or a negative number if it does
+// not fit LDS.  `items`: its work items (pixel tiles x channel tiles).
 template <int TM, int TN, int WPH, bool WDMA = false>
-bool fills(int n, int h, int w, int c_in, int c_out, bool win)
+double cost_one(int n, int h, int w, int c_in, int c_out, bool win, int64_t *items = nullptr)
 {
     ConvGeom g;
     size_t smem;
     bool lin;
-    if (!pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, g, smem, &lin)) return false;
-    return (int64_t)g.n_co_tiles * g.n_ptiles >= (lin ? 384 : 512);
+    const double cost = pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, g, smem, &lin);
+    if (items) *items = cost < 0 ? 0 : (int64_t)g.n_ptiles * g.n_co_tiles;
+    return cost;
 }
 
-// Largest block tile that fits LDS and still fills most of the 256 compute units.
 }  // namespace
 
 // The 256 x 128 tile of a channel width is compiled in a translation unit of its own (it is the
@@ -812,17 +830,40 @@ bnn_status launch_conv_big_tile(const uint32_t *in, const uint32_t *wt, int n, i
 
 namespace {
 
-// Which block tile launch_wph takes: the largest that fits LDS and still gives two resident
-// blocks per compute unit.  3: 256 x 128, 2: 128 x 128 with streamed weights, 1: 128 x 128,
+// 64-channel tiles of 256 and 128 pixels, for channel counts that leave half of a 128-channel tile
+// empty: weights resident, so up to twelve words per pixel.  (At two words the multiply phase is too
+// short for them to matter.)
+template <int WPH> constexpr bool narrow_tiles = WPH == 2 || WPH == 4 || WPH == 6;
+
+// Which block tile launch_wph takes: the one of least estimated cost.  The estimate is good to some
+// ten per cent (over 50 layers the tile it picks is the fastest one or within 5 % of it in all but
+// three), so the largest tile, which moves the least data, stays where it gives nearly every compute
+// unit two blocks unless another promises 15 % less.
+// us, largest / picked: 131 x 27 x 31, 256 -> 64 15.3 / 11.3 (256 x 64), 24 x 27 x 27, 400 -> 96
+// 19.6 / 14.3 (128 x 128), 100 x 16 x 16, 320 -> 320 23.8 / 17.0 (256 x 64), 64 x 8 x 8, 512 -> 512
+// 17.0 / 9.2 (64 x 64).
+// 3: 256 x 128, 2: 128 x 128 with streamed weights, 1: 128 x 128, 4: 256 x 64, 5: 128 x 64,
 // 0: 64 x 64.  win: a pooled layer (its tiles are made of 2x2 windows).
 template <int WPH>
 int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win)
 {
     // the larger tiles keep their weights resident (WPH <= 4) or stream them by DMA
     constexpr bool WD = WPH >= 6;
-    if (fills<4, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return 3;
-    if (fills<2, 2, WPH, WD>(n, h, w, c_in, c_out, win)) return WD ? 2 : 1;
-    return 0;
+    double best = -1;
+    int choice = 0;
+    auto take = [&](int c, double cost) {
+        if (cost >= 0 && (best < 0 || cost < best)) { best = cost; choice = c; }
+    };
+    int64_t items;
+    const double big = cost_one<4, 2, WPH, WD>(n, h, w, c_in, c_out, win, &items);
+    take(3, items >= 384 ? 0.85 * big : big);
+    take(WD ? 2 : 1, cost_one<2, 2, WPH, WD>(n, h, w, c_in, c_out, win));
+    if constexpr (narrow_tiles<WPH>) {
+        take(4, cost_one<4, 1, WPH>(n, h, w, c_in, c_out, win));
+        take(5, cost_one<2, 1, WPH>(n, h, w, c_in, c_out, win));
+    }
+    take(0, cost_one<1, 1, WPH>(n, h, w, c_in, c_out, win));
+    return choice;
 }
 
 template <int WPH>
@@ -834,6 +875,12 @@ bnn_status launch_wph(const uint32_t *in, const uint32_t *wt, int n, int h, int 
     case 3: return launch_conv_big_tile<WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
     case 2:
     case 1: return launch_one<2, 2, WPH, WD>(in, wt, n, h, w, c_in, c_out, ep, s);
+    case 4:
+        if constexpr (narrow_tiles<WPH>) return launch_one<4, 1, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
+        break;
+    case 5:
+        if constexpr (narrow_tiles<WPH>) return launch_one<2, 1, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
+        break;
     }
     return launch_one<1, 1, WPH>(in, wt, n, h, w, c_in, c_out, ep, s);
 }

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2301_05126_amd as P
 import workloads as W
-from tests.gpu_util import (DEV, DeviceModel, conv_binary_tiles, dev, empty_i32, fill_i32, host_u32,
+from tests.gpu_util import (DEV, DeviceModel, conv_binary_tiles, conv_kernel_choice, dev, empty_i32, fill_i32, host_u32,
                             pack_on_gpu, require_gpu)
 from tests.helpers import pack_pm1
 
@@ -363,6 +363,17 @@ def test_conv_binary_raster_tiles(n, h, w, ci, co):
         np.testing.assert_array_equal(host_u32(pk[:n]), pack_pm1(ref), err_msg=f"pool {pool} {pool_first}")
         assert int((pk[n] != -1).sum()) == 0
         np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
+
+
+# The 64-channel tiles of 256 (4) and 128 (5) pixels: each channel width that has them, at its ends;
+# one channel group, a ragged last one, several; rectangles and raster order.
+@pytest.mark.parametrize("n,h,w,ci,co,tile", [(1000, 10, 10, 100, 33, 4), (200, 14, 14, 65, 33, 5),
+                                              (64, 14, 14, 128, 129, 5), (100, 32, 32, 160, 33, 4),
+                                              (1000, 9, 9, 256, 33, 5), (100, 16, 16, 257, 320, 4),
+                                              (100, 32, 32, 384, 33, 4), (200, 16, 16, 384, 33, 5)])
+def test_conv_binary_narrow_tiles(n, h, w, ci, co, tile):
+    assert conv_kernel_choice(n, h, w, ci, co) == tile
+    test_conv_binary_raster_tiles(n, h, w, ci, co)
 
 
 # ------------------------------------------------------------------- conv_first_int8
