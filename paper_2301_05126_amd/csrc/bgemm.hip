@@ -31,6 +31,7 @@ namespace bnn {
 namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 // Four words of a row without branches, so that many such loads can be in flight together: a
 // word that does not exist reads the tensor's first word and is zeroed afterwards.
@@ -444,9 +445,11 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
 // row; lane half h owns words [8u + 4h, 8u + 4h + 4) of unit u, one 16-byte load per operand, lane
 // and unit).  Wave v takes the units v, v + 4, ... in rounds of up to eight units with all loads
 // of a round in flight together, straight from global memory (no staging, no barrier before the
-// MFMAs); the partial sums meet in LDS and wave 0 runs the epilogue.  Latency, not throughput:
-// with a quarter of K per wave and four times the blocks, a batch-256 FC layer of K = 8192 takes
-// half the time of the 64 x 64 tile.
+// MFMAs); the partial sums meet in LDS, and each wave adds up and finishes eight of the 32 rows.
+// Latency, not throughput: with a quarter of K per wave and four times the blocks, a batch-256 FC
+// layer of K = 8192 takes half the time of the 64 x 64 tile.  The block's last part is a serial chain,
+// so it is split: wave 0 alone, with thresholds fetched after the sums, took 0.8 us more (device us,
+// before / after: 64 x 512, K = 512 3.6 / 2.9; 256 x 1024, K = 8192 6.1 / 5.4).
 //
 // TAIL (see bgemv_rows): the block's 32 output words, one per row, each give their share of at
 // most 16 logits per row; thread t adds those of row t % 32 and classes t / 32 and t / 32 + 8.
@@ -456,7 +459,7 @@ __global__ __launch_bounds__(256) void bgemm_small(const uint32_t *__restrict__ 
                                                    FcTailArgs tail)
 {
     constexpr int UR = 8;                   // units per wave and round
-    __shared__ float red[3][16][64];        // partial sums of waves 1..3
+    __shared__ v4f red[4][4][64];           // partial sums: [wave][four registers][lane]
     __shared__ uint32_t out_word[32];
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
@@ -472,6 +475,14 @@ __global__ __launch_bounds__(256) void bgemm_small(const uint32_t *__restrict__ 
             const int j = (t >> 5) + 8 * i;
             if (j < tail.n_out) w_tail[i] = tail.w[(int64_t)j * ((N + 31) >> 5) + (n0 >> 5)];
         }
+    }
+    const int64_t col = n0 + l32;
+    const bool cok = col < N;
+    int thr = 0;                            // (these too)
+    unsigned flipv = 0;
+    if (ep.packed) {
+        thr = ep.thr[cok ? col : 0];
+        if (ep.flip) flipv = ep.flip[cok ? col : 0];
     }
 
     uint32_t sgn = 0x88888888u, one = 0x22222222u;
@@ -501,43 +512,34 @@ __global__ __launch_bounds__(256) void bgemm_small(const uint32_t *__restrict__ 
             }
         }
     }
-    if (wave > 0) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[wave - 1][r][lane] = acc[r];
-    }
+    for (int q = 0; q < 4; ++q) red[wave][q][lane] = v4f{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
     __syncthreads();
-    if (wave == 0) {
+    {
+        // register r of lane (l32, half) is row 8(r/4) + 4*half + r%4, column l32; this wave's are the
+        // registers 4 * wave .. 4 * wave + 3 (small integers: exact in any order)
+        v4f sum = red[0][wave][lane];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-#pragma unroll
-            for (int v = 0; v < 3; ++v) acc[r] += red[v][r][lane];      // small integers: exact in any order
-
-        // ---- epilogue of one 32 x 32 tile: register r of lane (l32, half) is row 8(r/4) + 4*half + r%4, column l32
+        for (int v = 1; v < 4; ++v) sum += red[v][wave][lane];
         const int corr = units * 8 * 32 - K;        // zero words and tail bits all counted as +1
-        const int64_t rbase = m0 + half * 4, col = n0 + l32;
-        const bool cok = col < N;
+        const int r0 = wave * 8 + half * 4;
         if (ep.preact) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = rbase + (r >> 2) * 8 + (r & 3);
-                if (row < M && cok) ep.preact[row * N + col] = (int)acc[r] - corr;
-            }
+            for (int i = 0; i < 4; ++i)
+                if (m0 + r0 + i < M && cok) ep.preact[(m0 + r0 + i) * N + col] = (int)sum[i] - corr;
         }
         if (ep.packed) {
             const int64_t nw = (N + 31) >> 5;
-            const int thr = cok ? ep.thr[col] : 0;
-            const bool flip = cok && ep.flip && ep.flip[col];
             unsigned mine = 0;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int x = (int)acc[r] - corr;
-                const unsigned long long mask = __ballot(cok && ((x > thr) != flip));
+            for (int i = 0; i < 4; ++i) {
+                const int x = (int)sum[i] - corr;
+                const unsigned long long mask = __ballot(cok && ((x > thr) != (flipv != 0)));
                 const unsigned word = half ? (unsigned)(mask >> 32) : (unsigned)mask;
-                if (l32 == r) mine = word;          // lane r of each half keeps the word of register r
+                if (l32 == i) mine = word;          // lane i of each half keeps the word of its row i
             }
-            const int64_t row = rbase + (l32 >> 2) * 8 + (l32 & 3);
-            if (l32 < 16 && row < M) ep.packed[row * nw + (n0 >> 5)] = mine;
-            if (TAIL && l32 < 16) out_word[half * 4 + (l32 >> 2) * 8 + (l32 & 3)] = mine;
+            if (l32 < 4 && m0 + r0 + l32 < M) ep.packed[(m0 + r0 + l32) * nw + (n0 >> 5)] = mine;
+            if (TAIL && l32 < 4) out_word[r0 + l32] = mine;
         }
     }
     if (TAIL) {
