@@ -92,8 +92,8 @@ def time_steps_streams(models, x, P, steps, warmup, torch):
 
 def time_captured(fn, n, torch, replays=5):
     """Per-launch device period of n launches captured once into a graph and replayed: one
-    binding call costs the host about 7 us (ctypes marshalling), more than a small kernel
-    runs, so a host-issued loop measures the host.  Returns ms per launch."""
+    binding call costs the host about 4 us (ctypes marshalling), more than the smallest kernels
+    run, so a host-issued loop measures the host.  Returns ms per launch."""
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
