@@ -802,7 +802,12 @@ bnn_status launch_fc_binary(const uint32_t *a, int64_t m, int64_t k, const uint3
     const int64_t want = 192;
     auto reach = [&](int rows) { return !ep.preact || rows * n < (int64_t)1 << 29; };
     const bool both = ep.preact && ep.packed;       // diagnostic calls: the 256 x 256 tile would spill
-    if (!both && ceil_div64(m, 256) * ceil_div64(n, 256) >= want && reach(256))
+    // Raw sums of a short K are mostly stores, which the 128 x 128 tile's two blocks per compute unit overlap
+    // with each other's multiplies (us, 256 x 256 / 128 x 128: 6000 x 6000, K = 640 41.1 / 31.1; 5000 x 5000, K =
+    // 1024 29.2 / 25.3; 4096 x 4096, K = 1024 18.7 / 18.1); an output around the size of the memory-side cache or
+    // larger favours the larger tile again (8000 x 8000, K = 512 56.3 / 60.1; 12000 x 8000, K = 1024 84 / 95).
+    const bool stores = ep.preact && k <= 1024 && m * n <= (int64_t)3 << 24;
+    if (!both && !stores && ceil_div64(m, 256) * ceil_div64(n, 256) >= want && reach(256))
         return launch_mfma<4, 4>(a, m, k, b, n, kw, ep, s);
     if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want && reach(128))
         return launch_mfma<2, 2>(a, m, k, b, n, kw, ep, s);

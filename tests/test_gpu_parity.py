@@ -199,6 +199,12 @@ def test_fc_binary_tile_rounds(m, n, k):
     np.testing.assert_array_equal(host_u32(packed2), bits)
 
 
+# Raw sums just past the K up to which they take the 128 x 128 tile: several 256 x 256 tiles per block.
+@pytest.mark.parametrize("m,n,k", [(4097, 4352, 1025), (4352, 4356, 1152)])
+def test_fc_binary_raw_tile_by_k(m, n, k):
+    test_fc_binary_tile_rounds(m, n, k)
+
+
 def test_fc_binary_with_gpu_packed_operands_and_empty_batch():
     rng = rng_of(77)
     a, b = pm1(rng, (70, 777)), pm1(rng, (90, 777))
