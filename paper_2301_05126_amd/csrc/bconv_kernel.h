@@ -80,6 +80,45 @@ constexpr bool weights_resident(int tm, int tn, int wph)
     return bytes <= 40 * 1024 || (tm * tn == 1 && bytes <= 48 * 1024);
 }
 
+// WDMA: the weight word that a lane delivers with transfer k (0..7) of a chunk.  A chunk buffer's row
+// holds 16 words, eight places for each lane half of which the first SPC are used; transfer k of wave
+// `wave` fills rows 4 * (wave + 4k) .. +3 of it.  The word's address is voff() + chunk_offset(), the
+// latter (and k's rows, where the layer is exact) in the scalar offset.  A scalar offset need not take
+// part in the buffer's range check, so a lane that has no word must say so in the vector offset: with
+// six words per half, places 6 and 7 would otherwise read the next tap's first words, and behind
+// the last tap of the last channel eight bytes past the tensor.
+template <int WPH>
+struct WeightLane {
+    static constexpr int SPC = steps_per_chunk(WPH);
+    static constexpr unsigned NONE = 0x80000000u;          // past the end of any weight tensor (< 2 GiB)
+    unsigned first;                                        // transfer 0
+    bool place, ok[2];                                     // the place is used; the word exists (even / odd chunk)
+
+    __host__ __device__ __forceinline__ WeightLane(int o_blk, int wave, int lane, int cw)
+    {
+        const int phys = (lane & 15) >> 1, sub = lane & 1;
+        const int lw = ((phys ^ ((2 * wave + (lane >> 5)) & 7)) << 1) | sub;    // logical word of the chunk row
+        const int hh = lw >> 3, st = lw & 7;
+        first = (unsigned)(((o_blk + 4 * wave + (lane >> 4)) * 9 * cw + hh * WPH + st) * 4);
+        place = st < SPC;
+        ok[0] = place && hh * WPH + st < cw;
+        ok[1] = place && hh * WPH + st + (WPH > 8 ? 8 : 0) < cw;
+    }
+    __host__ __device__ static __forceinline__ unsigned chunk_offset(int chunk, int cw)
+    {
+        const int s0 = chunk * SPC;
+        return (unsigned)(((s0 / WPH) * cw + s0 % WPH) * 4);
+    }
+    // bytes between the rows of transfers k and k + 1
+    __host__ __device__ static __forceinline__ unsigned row_step(int cw) { return (unsigned)(16 * 9 * 4) * (unsigned)cw; }
+    // exact: 2 * WPH words per pixel and whole channel tiles, every place's row exists
+    __host__ __device__ __forceinline__ unsigned voff_exact() const { return place ? first : NONE; }
+    __host__ __device__ __forceinline__ unsigned voff(int chunk, int k, int cw) const
+    {
+        return (WPH > 8 && (chunk & 1) ? ok[1] : ok[0]) ? first + k * row_step(cw) : NONE;
+    }
+};
+
 struct TileCoord {
     int group, ty, tx;           // image group, tile row, tile column (LIN: first image, first unit inside it, -)
 };
@@ -261,37 +300,25 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     auto load_w = [&](int chunk) { load_w_to(chunk, pb); };
     auto store_w = [&](int buf) { store_w_from(buf, pb); };
 
-    // WDMA: instruction k (0..7) of this wave fills LDS words [(wave + 4k) * 64, +64) of a
-    // chunk buffer = rows 4*(wave + 4k) .. +3.  The word a lane delivers depends on k and on
-    // the chunk only through a scalar offset.
-    unsigned wd_voff = 0;
-    bool wd_ok[2] = {true, true};                          // the lane's word exists (even / odd chunk)
+    // WDMA: a chunk's transfers (which word a lane delivers: see WeightLane)
     v4i wd_rsrc = make_raw_rsrc(wt, (unsigned)g.c_out * 9u * (unsigned)g.cw * 4u);
-    if (WDMA) {
-        const int phys = (lane & 15) >> 1, sub = lane & 1;
-        const int lw = ((phys ^ ((2 * wave + (lane >> 5)) & 7)) << 1) | sub;    // logical word of the chunk row
-        const int hh = lw >> 3, st = lw & 7;
-        wd_voff = (unsigned)(((o_blk + 4 * wave + (lane >> 4)) * 9 * g.cw + hh * WPH + st) * 4);
-        wd_ok[0] = st < SPC && hh * WPH + st < g.cw;
-        wd_ok[1] = st < SPC && hh * WPH + st + (WPH > 8 ? 8 : 0) < g.cw;
-    }
+    const WeightLane<WPH> wd(o_blk, wave, lane, g.cw);
+    const unsigned wd_exact = wd.voff_exact();
     auto dma_w = [&](int chunk, int buf) {
-        const int s0 = chunk * SPC;
         // (wave-uniform; read through readfirstlane so that it reaches the transfer's scalar
         // operand in a scalar register whatever the compiler makes of the chunk index)
-        const unsigned soff0 = (unsigned)__builtin_amdgcn_readfirstlane(((s0 / WPH) * g.cw + (s0 % WPH)) * 4);
+        const unsigned soff0 = (unsigned)__builtin_amdgcn_readfirstlane((int)wd.chunk_offset(chunk, g.cw));
         const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) uint32_t *)(Bs + buf * BN * LSB) +
                              (unsigned)__builtin_amdgcn_readfirstlane(wave) * 256u;
-        const unsigned rows16 = (unsigned)(16 * 9 * 4) * (unsigned)g.cw;
+        const unsigned rows16 = wd.row_step(g.cw);
         if (g.wexact) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) lds_dma4_soff(wd_rsrc, dst + k * 1024u, wd_voff, soff0 + k * rows16);
+            for (int k = 0; k < 8; ++k) lds_dma4_soff(wd_rsrc, dst + k * 1024u, wd_exact, soff0 + k * rows16);
         } else {
             // the row in the vector offset, where the range check sees it
-            const bool ok = WPH > 8 && (chunk & 1) ? wd_ok[1] : wd_ok[0];
 #pragma unroll
             for (int k = 0; k < 8; ++k)
-                lds_dma4_soff(wd_rsrc, dst + k * 1024u, ok ? wd_voff + k * rows16 : 0x80000000u, soff0);
+                lds_dma4_soff(wd_rsrc, dst + k * 1024u, wd.voff(chunk, k, g.cw), soff0);
         }
     };
     // this lane's read offsets (words) inside a weight row, per V-step group

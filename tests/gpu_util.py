@@ -58,6 +58,8 @@ def hooks():
         _hooks.bnn_test_conv_binary_tiles.restype = C.c_int
         _hooks.bnn_test_conv_binary_kernel_choice.argtypes = [C.c_int] * 6
         _hooks.bnn_test_conv_binary_kernel_choice.restype = C.c_int
+        _hooks.bnn_test_conv_weight_reads.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int64)]
+        _hooks.bnn_test_conv_weight_reads.restype = C.c_int64
     return _hooks
 
 
@@ -77,3 +79,12 @@ KERNEL_SMALL, TILE_256x128, TILE_128x128_STREAMED, TILE_128x128, TILE_64x64 = 10
 def conv_kernel_choice(n, h, w, c_in, c_out, tiles_only=False):
     """Which kernel a binary convolution of this shape runs on (host-side query, no GPU work)."""
     return hooks().bnn_test_conv_binary_kernel_choice(n, h, w, c_in, c_out, 1 if tiles_only else 0)
+
+
+def conv_weight_reads(c_in, c_out):
+    """(bytes behind the weight tensor that the streamed transfers read, <= 0: none; words of the
+    tensor that none delivers), by the kernel's own address functions on the host."""
+    import ctypes as C
+    missed = C.c_int64(-1)
+    past = hooks().bnn_test_conv_weight_reads(c_in, c_out, C.byref(missed))
+    return past, missed.value

@@ -13,7 +13,7 @@ def build() -> str:
     cmd = [HIPCC, "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(PKG, "csrc"),
-           os.path.join(HERE, "conv_tiles_hook.hip"), "-o", LIB,
+           os.path.join(HERE, "conv_tiles_hook.hip"), os.path.join(HERE, "conv_weights_hook.hip"), "-o", LIB,
            "-L" + PKG, "-lbnn", "-Wl,-rpath,$ORIGIN/../../paper_2301_05126_amd"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

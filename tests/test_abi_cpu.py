@@ -201,6 +201,17 @@ def test_kernel_choice_of_the_benchmark_shapes(lib):
     assert conv_kernel_choice(4, 8, 8, 2048, 32) == -1       # more than 1024 channels: unsupported
 
 
+@pytest.mark.parametrize("c_in", [257, 288, 352, 353, 384, 385, 480, 512, 513, 800, 992, 1024])
+@pytest.mark.parametrize("c_out", [1, 127, 128, 256, 300])
+def test_streamed_weights_stay_inside_the_tensor(lib, c_in, c_out):
+    # host-side walk over the addresses of the convolution's weight transfers: each word of the tensor
+    # is delivered, and nothing behind its last word is read, also where a place of the LDS row has
+    # no word of its own (twelve words per pixel)
+    from tests.gpu_util import conv_weight_reads
+    past, missed = conv_weight_reads(c_in, c_out)
+    assert past <= 0 and missed == 0
+
+
 def test_run_model_noalloc_validation(lib):
     # the entry point without a workspace argument refuses, on the host and before any HIP call,
     # what does not fit its fixed device array
