@@ -78,6 +78,7 @@ struct GemmWalk {
     int nbm, nbn;            // tiles along M and N
     int tiles;               // nbm * nbn
     int stream;              // 1: streaming stores of raw sums
+    int far;                 // raw sums: 32-bit offsets reach over a tile's rows (0), over eight rows (1), or not (2)
 };
 
 // Persistent blocks.  Tile numbers run column-major inside bands of eight tile rows; each XCD takes
@@ -113,7 +114,8 @@ struct GemmWalk {
 constexpr int KC = 16, NBUF = 4, XW = 32 * 32;
 
 // RAW / PACKED: which outputs the instance writes (one of the two in all but diagnostic calls).
-template <int TM, int TN, int VEC, int OCC, bool RAW, bool PACKED>
+// FAR: raw sums whose rows are so long that 32-bit offsets do not reach over a tile's.
+template <int TM, int TN, int VEC, int OCC, bool RAW, bool PACKED, bool FAR>
 __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restrict__ A,
                                                       const uint32_t *__restrict__ B, int64_t M, int64_t N,
                                                       int Kw, int K, GemmWalk gw, EpiArgs ep)
@@ -326,9 +328,10 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
             // row r at position c ^ (r % 8): no bank conflicts either way) and reads quad lane % 8 of
             // rows lane / 8 + 8k.  Whole cache lines matter: quads stored as they come out of the
             // accumulators (32 bytes to a row) take 308 us at 8192^3, 64 bytes to a row 212 us, this
-            // 195 us.  The stores go through a buffer resource over the tile's rows of C (the launcher
-            // sees to it that 32-bit offsets reach them): a row past M or a column past N addresses past
-            // its end and is dropped.
+            // 195 us.  The stores go through a buffer resource over the tile's rows of C, or (FAR) over
+            // eight of them at a time: a row past M or a column past N addresses past its end and is dropped.
+            // Where not even eight rows fit, 64-bit addresses.  (FAR is apart: eight rows at a time always
+            // takes up to 7 % longer, and all three in one instance spill scalar registers.)
             const unsigned c_row = (unsigned)N * 4u;
             const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
                 ep.preact + m0 * N, 0, (int)((unsigned)rows * c_row), 0x00020000);
@@ -360,7 +363,60 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                         asm volatile("" ::: "memory");
                         __builtin_amdgcn_sched_barrier(0);      // one tile's registers at a time
                     }
-                    if (whole) {
+                    const int r0 = wm * TM * 32 + i * 32;
+                    if constexpr (FAR) {
+                        if (gw.far == 1) {
+                            const unsigned at8 = (unsigned)sr * c_row + col * 4u;
+                            auto rows8 = [&](int k) {
+                                const int left = rows - (r0 + 8 * k);
+                                return __builtin_amdgcn_make_buffer_rsrc(
+                                    ep.preact + (m0 + r0 + 8 * k) * N, 0,
+                                    (int)((unsigned)(left < 0 ? 0 : (left < 8 ? left : 8)) * c_row), 0x00020000);
+                            };
+                            if (whole) {
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) {
+                                    const __amdgpu_buffer_rsrc_t c8 = rows8(k);
+#pragma unroll
+                                    for (int j = 0; j < GJ; ++j) {
+                                        const int jj = j0 + j;
+                                        const unsigned aj = col + jj * 32 < (unsigned)N ? at8 + jj * 128 : 0x80000000u;
+                                        if (gw.stream) __builtin_amdgcn_raw_buffer_store_b128(x[j][k], c8, aj, 0, 2);
+                                        else __builtin_amdgcn_raw_buffer_store_b128(x[j][k], c8, aj, 0, 0);
+                                    }
+                                }
+                            } else {
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) {
+                                    const __amdgpu_buffer_rsrc_t c8 = rows8(k);
+#pragma unroll
+                                    for (int j = 0; j < GJ; ++j)
+#pragma unroll
+                                        for (int e = 0; e < 4; ++e) {
+                                            const int jj = j0 + j;
+                                            const unsigned ae =
+                                                col + jj * 32 + e < (unsigned)N ? at8 + (jj * 128 + e * 4) : 0x80000000u;
+                                            __builtin_amdgcn_raw_buffer_store_b32(x[j][k][e], c8, ae, 0, 0);
+                                        }
+                                }
+                            }
+                        } else {
+                            int32_t *cp = ep.preact + (m0 + r0 + sr) * N + n0 + col0 + j0 * 32 + sq * 4;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k, cp += 8 * N)
+#pragma unroll
+                                for (int j = 0; j < GJ; ++j) {
+                                    const int64_t left = r0 + sr + k * 8 < rows ? N - (n0 + col0 + (j0 + j) * 32 + sq * 4) : 0;
+                                    if (left >= 4 && (N & 3) == 0) {
+                                        *reinterpret_cast<v4i *>(cp + j * 32) = x[j][k];
+                                    } else {
+#pragma unroll
+                                        for (int e = 0; e < 4; ++e)
+                                            if (e < left) cp[j * 32 + e] = x[j][k][e];
+                                    }
+                                }
+                        }
+                    } else if (whole) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -386,7 +442,7 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                 }
                 at += 32 * c_row;
             }
-            after_stores = whole && !PACKED;
+            after_stores = whole && !PACKED && (!FAR || gw.far == 1);
         }
         if constexpr (PACKED) {
             // thresholds through LDS (written and read by the same wave) into the accumulators' channel
@@ -688,10 +744,13 @@ __global__ __launch_bounds__(512) void bgemv_rows(const uint32_t *__restrict__ A
     }
 }
 
-template <int TM, int TN, int VEC, bool RAW, bool PACKED>
+template <int TM, int TN, int VEC, bool RAW, bool PACKED, bool FAR = false>
 bnn_status launch_mfma_out(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n, int kw,
                            const GemmWalk &gw, const EpiArgs &ep, hipStream_t s)
 {
+    if constexpr (RAW && !FAR) {
+        if (gw.far) return launch_mfma_out<TM, TN, VEC, RAW, PACKED, true>(a, m, k, b, n, kw, gw, ep, s);
+    }
     // blocks per compute unit: the 256 x 256 tile fills the registers, the smaller ones the LDS
     constexpr int OCC = TM * TN >= 16 ? 1 : 2;
     constexpr int RES = TM * TN >= 16 ? 1 : (TM * TN >= 4 ? 2 : 3);
@@ -701,14 +760,14 @@ bnn_status launch_mfma_out(const uint32_t *a, int64_t m, int64_t k, const uint32
         static std::once_flag once;
         static hipError_t raise_err = hipSuccess;
         std::call_once(once, [] {
-            raise_err = hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED>,
+            raise_err = hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         });
         if (raise_err != hipSuccess) return hip_result(raise_err);
     }
     // a whole number of blocks per XCD; those without a tile leave at once
     const unsigned blocks = 8u * (unsigned)ceil_div64(gw.tiles < 256 * RES ? gw.tiles : 256 * RES, 8);
-    hipLaunchKernelGGL((bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED>), dim3(blocks), dim3(256), smem, s, a, b, m, n, kw,
+    hipLaunchKernelGGL((bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>), dim3(blocks), dim3(256), smem, s, a, b, m, n, kw,
                        (int)k, gw, ep);
     return hip_result(hipGetLastError());
 }
@@ -736,6 +795,7 @@ bnn_status launch_mfma(const uint32_t *a, int64_t m, int64_t k, const uint32_t *
     // without).  The 256 x 256 tile: where C is larger than the 256 MiB memory-side cache (12000 x 8000,
     // K = 1024: 84.5 us with, 88.5 without; 8000 x 8000, K = 512: 54 with, 48 without).
     gw.stream = (n & 31) == 0 && (TM * TN < 16 || m * n > (int64_t)1 << 26);
+    gw.far = 64 * TM * n < (int64_t)1 << 29 ? 0 : (n < (int64_t)1 << 26 ? 1 : 2);
     if ((kw & 3) == 0) return launch_mfma_vec<TM, TN, 4>(a, m, k, b, n, kw, gw, ep, s);
     return launch_mfma_vec<TM, TN, 1>(a, m, k, b, n, kw, gw, ep, s);
 }
@@ -788,35 +848,44 @@ bnn_status launch_gemv(const uint32_t *a, int64_t m, int64_t k, const uint32_t *
 
 }  // namespace
 
+int fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, bool raw, bool packed)
+{
+    if (m <= 8) return FC_GEMV;
+    // largest tile that still fills most of the 256 compute units
+    const int64_t want = 192;
+    const bool both = raw && packed;                // diagnostic calls: the 256 x 256 tile would spill
+    // Raw sums of millions of columns: there are tiles enough of any size, and the padding of the rows decides
+    // (us, 256 x 256 / as chosen, n = 2^21: m = 9, K = 4096 847 / 374; m = 100, K = 64 390 / 180; m = 300, K = 4096
+    // 1752 / 1484; at m = 512, K = 4096 the 256 x 256 tile takes 1900, the 128 x 128 one 2050).
+    if (raw && n >= (int64_t)1 << 21) {
+        if (m <= 64) return FC_TILE_64;
+        return both || ceil_div64(m, 128) * 128 * 6 < ceil_div64(m, 256) * 256 * 5 ? FC_TILE_128 : FC_TILE_256;
+    }
+    // Raw sums of a short K are mostly stores, which the 128 x 128 tile's two blocks per compute unit overlap
+    // with each other's multiplies (us, 256 x 256 / 128 x 128: 6000 x 6000, K = 640 41.1 / 31.1; 5000 x 5000, K =
+    // 1024 29.2 / 25.3; 4096 x 4096, K = 1024 18.7 / 18.1); an output around the size of the memory-side cache or
+    // larger favours the larger tile again (8000 x 8000, K = 512 56.3 / 60.1; 12000 x 8000, K = 1024 84 / 95).
+    const bool stores = raw && k <= 1024 && m * n <= (int64_t)3 << 24;
+    if (!both && !stores && ceil_div64(m, 256) * ceil_div64(n, 256) >= want) return FC_TILE_256;
+    if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want) return FC_TILE_128;
+    // fewer than that many 64 x 64 tiles: 32 x 32 tiles with K split over the block's waves
+    return fc_takes_small_kernel(m, n) ? FC_SMALL : FC_TILE_64;
+}
+
 bnn_status launch_fc_binary(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n,
                             const EpiArgs &ep, hipStream_t s)
 {
     if (m == 0) return BNN_OK;
     const int kw = (int)((k + 31) / 32);
-    if (m <= 8) {
-        const FcTailArgs none = {nullptr, nullptr, 0};
-        return launch_gemv<false>(a, m, k, b, n, kw, ep, none, s);
+    const FcTailArgs none = {nullptr, nullptr, 0};
+    switch (fc_binary_kernel_choice(m, k, n, ep.preact != nullptr, ep.packed != nullptr)) {
+    case FC_GEMV: return launch_gemv<false>(a, m, k, b, n, kw, ep, none, s);
+    case FC_SMALL: return launch_small<false>(a, m, k, b, n, kw, ep, none, s);
+    case FC_TILE_64: return launch_mfma<1, 1>(a, m, k, b, n, kw, ep, s);
+    case FC_TILE_128: return launch_mfma<2, 2>(a, m, k, b, n, kw, ep, s);
+    case FC_TILE_256: return launch_mfma<4, 4>(a, m, k, b, n, kw, ep, s);
     }
-    // largest tile that still fills most of the 256 compute units (and whose rows of raw output a
-    // 32-bit offset reaches: the kernels' stores go through a buffer resource over them)
-    const int64_t want = 192;
-    auto reach = [&](int rows) { return !ep.preact || rows * n < (int64_t)1 << 29; };
-    const bool both = ep.preact && ep.packed;       // diagnostic calls: the 256 x 256 tile would spill
-    // Raw sums of a short K are mostly stores, which the 128 x 128 tile's two blocks per compute unit overlap
-    // with each other's multiplies (us, 256 x 256 / 128 x 128: 6000 x 6000, K = 640 41.1 / 31.1; 5000 x 5000, K =
-    // 1024 29.2 / 25.3; 4096 x 4096, K = 1024 18.7 / 18.1); an output around the size of the memory-side cache or
-    // larger favours the larger tile again (8000 x 8000, K = 512 56.3 / 60.1; 12000 x 8000, K = 1024 84 / 95).
-    const bool stores = ep.preact && k <= 1024 && m * n <= (int64_t)3 << 24;
-    if (!both && !stores && ceil_div64(m, 256) * ceil_div64(n, 256) >= want && reach(256))
-        return launch_mfma<4, 4>(a, m, k, b, n, kw, ep, s);
-    if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want && reach(128))
-        return launch_mfma<2, 2>(a, m, k, b, n, kw, ep, s);
-    // fewer than that many 64 x 64 tiles: 32 x 32 tiles with K split over the block's waves
-    if (fc_takes_small_kernel(m, n) || !reach(64)) {
-        const FcTailArgs none = {nullptr, nullptr, 0};
-        return launch_small<false>(a, m, k, b, n, kw, ep, none, s);
-    }
-    return launch_mfma<1, 1>(a, m, k, b, n, kw, ep, s);
+    return BNN_ERR_UNSUPPORTED;
 }
 
 bool fc_binary_tail_qualifies(int64_t m, int64_t n, int64_t n_out)

@@ -50,6 +50,9 @@ bnn_status launch_threshold_sign_maxpool(const int32_t *x, int n, int h, int w, 
                                          int pool_first, uint32_t *out, hipStream_t s);
 bnn_status launch_fc_binary(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n,
                             const EpiArgs &ep, hipStream_t s);
+// Which kernel launch_fc_binary takes (host-side query, launches nothing); raw / packed: the outputs asked for.
+enum { FC_GEMV = 0, FC_SMALL = 1, FC_TILE_64 = 2, FC_TILE_128 = 3, FC_TILE_256 = 4 };
+int fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, bool raw, bool packed);
 // launch_fc_binary with the following (last, step-less) layer of n_out classes folded in, for the
 // shapes that run on bgemv_rows or bgemm_small; fc_binary_tail_qualifies says which those are.
 // The logits (m x n_out <= FC_TAIL_MAX_LOGITS words) are zeroed on the side by an earlier launch.

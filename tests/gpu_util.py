@@ -58,6 +58,8 @@ def hooks():
         _hooks.bnn_test_conv_binary_tiles.restype = C.c_int
         _hooks.bnn_test_conv_binary_kernel_choice.argtypes = [C.c_int] * 6
         _hooks.bnn_test_conv_binary_kernel_choice.restype = C.c_int
+        _hooks.bnn_test_fc_binary_kernel_choice.argtypes = [C.c_int64] * 3 + [C.c_int] * 2
+        _hooks.bnn_test_fc_binary_kernel_choice.restype = C.c_int
         _hooks.bnn_test_conv_weight_reads.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_int64)]
         _hooks.bnn_test_conv_weight_reads.restype = C.c_int64
     return _hooks
@@ -88,3 +90,11 @@ def conv_weight_reads(c_in, c_out):
     missed = C.c_int64(-1)
     past = hooks().bnn_test_conv_weight_reads(c_in, c_out, C.byref(missed))
     return past, missed.value
+
+
+FC_GEMV, FC_SMALL, FC_TILE_64, FC_TILE_128, FC_TILE_256 = 0, 1, 2, 3, 4
+
+
+def fc_kernel_choice(m, n, k, raw=True, packed=False):
+    """Which kernel bnn_fc_binary runs a product on (host-side query, no GPU work)."""
+    return hooks().bnn_test_fc_binary_kernel_choice(m, k, n, 1 if raw else 0, 1 if packed else 0)

@@ -24,3 +24,10 @@ extern "C" int bnn_test_conv_binary_kernel_choice(int n, int h, int w, int c_in,
 {
     return bnn::conv_binary_kernel_choice(n, h, w, c_in, c_out, tiles_only != 0);
 }
+
+// Which kernel bnn_fc_binary runs a product on: 0 = m <= 8 rows, 1 = 32 x 32 tiles with K split over the
+// waves, 2 / 3 / 4 = persistent 64 x 64, 128 x 128, 256 x 256 tiles.  Host-only.
+extern "C" int bnn_test_fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, int raw, int packed)
+{
+    return bnn::fc_binary_kernel_choice(m, k, n, raw != 0, packed != 0);
+}

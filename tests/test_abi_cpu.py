@@ -201,6 +201,19 @@ def test_kernel_choice_of_the_benchmark_shapes(lib):
     assert conv_kernel_choice(4, 8, 8, 2048, 32) == -1       # more than 1024 channels: unsupported
 
 
+def test_kernel_choice_of_products_with_many_columns(lib):
+    # the number of columns does not take a product off the tile kernels
+    from tests.gpu_util import FC_TILE_64, FC_TILE_128, FC_TILE_256, fc_kernel_choice
+    for n in (1 << 20, (1 << 21) + 5, 1 << 22, 1 << 23, 1 << 26, 1 << 31):
+        for k in (64, 2048):
+            assert fc_kernel_choice(500, n, k, True, False) == FC_TILE_256, n
+            assert fc_kernel_choice(500, n, k, False, True) == FC_TILE_256, n
+            assert fc_kernel_choice(300, n, k, True, True) == FC_TILE_128, n
+    for n in ((1 << 21) + 5, 1 << 23, 1 << 31):
+        assert fc_kernel_choice(128, n, 2048, True, False) == FC_TILE_128, n
+        assert fc_kernel_choice(64, n, 2048, True, False) == FC_TILE_64, n
+
+
 @pytest.mark.parametrize("c_in", [257, 288, 352, 353, 384, 385, 480, 512, 513, 800, 992, 1024])
 @pytest.mark.parametrize("c_out", [1, 127, 128, 256, 300])
 def test_streamed_weights_stay_inside_the_tensor(lib, c_in, c_out):

@@ -10,7 +10,8 @@ import torch
 import oracle
 import paper_2301_05126_amd as P
 import workloads as W
-from tests.gpu_util import DeviceModel, dev, fill_i32, host_u32, pack_on_gpu, require_gpu
+from tests.gpu_util import (FC_TILE_64, FC_TILE_128, FC_TILE_256, DeviceModel, dev, fc_kernel_choice, fill_i32,
+                            host_u32, pack_on_gpu, require_gpu)
 from tests.helpers import pack_pm1, unpack_words
 
 pytestmark = pytest.mark.gpu
@@ -92,6 +93,45 @@ def test_gemm_large_freivalds_rows_cols_samples(size, layer):
     for _ in range(256):                             # and single dots at unstructured positions
         i, j = int(rng.integers(m)), int(rng.integers(n))
         assert c[i, j] == oracle.dot(a[i], b[j])
+
+
+# Raw sums whose rows are so long that 32-bit offsets do not reach over a tile's (from 2^21, 2^22 and 2^23
+# columns on for tiles of 256, 128 and 64 rows; over eight rows from 2^26 on), with columns that end inside a quad and on one; the
+# reference is the product of the unpacked operands in FP32 (integers below 2^24: exact).
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("m,n,k,both,tile", [(200, (1 << 21) + 5, 64, False, FC_TILE_256),
+                                             (513, (1 << 21) + 64, 70, False, FC_TILE_256),
+                                             (140, (1 << 21) + 36, 1100, False, FC_TILE_256),
+                                             (65, (1 << 22) + 7, 1000, False, FC_TILE_128),
+                                             (130, (1 << 22) + 8, 32, True, FC_TILE_128),
+                                             (9, (1 << 23) + 12, 600, False, FC_TILE_64),
+                                             (11, (1 << 23) + 33, 96, True, FC_TILE_64),
+                                             (9, (1 << 26) + 36, 32, False, FC_TILE_64),
+                                             (66, (1 << 26) + 6, 32, False, FC_TILE_128)])
+def test_gemm_raw_with_many_columns(m, n, k, both, tile):
+    assert fc_kernel_choice(m, n, k, True, both) == tile
+    print("many columns", m, n, k, both, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    a, b = (2 * torch.randint(0, 2, (r, k), dtype=torch.int8, generator=g, device="cuda") - 1 for r in (m, n))
+    kw = (k + 31) // 32
+    ad, bd = fill_i32((m, kw), 0), fill_i32((n, kw), 0)
+    P.bnn_pack_bits(a, m, k, ad)
+    P.bnn_pack_bits(b, n, k, bd)
+    c = fill_i32((m + 1, n), 123456)
+    thr = torch.randint(-9, 10, (n,), dtype=torch.int32, generator=g, device="cuda")
+    packed = fill_i32((m, (n + 31) // 32), -1)
+    if both:
+        P.bnn_fc_binary(ad, m, k, bd, n, thr=thr, packed_out=packed, c_out=c)
+    else:
+        P.bnn_fc_binary(ad, m, k, bd, n, c_out=c)
+    af = a.float()
+    for j in range(0, n, 1 << 18):
+        want = (af @ b[j:j + (1 << 18)].float().t().contiguous()).int()
+        assert torch.equal(c[:m, j:j + (1 << 18)], want), j
+        if both:
+            bits = (want > thr[j:j + (1 << 18)]).cpu().numpy()
+            np.testing.assert_array_equal(host_u32(packed[:, j // 32:(j + (1 << 18)) // 32]), pack_pm1(bits.astype(np.int8)))
+    assert bool((c[m] == 123456).all())
 
 
 @pytest.mark.timeout(300)
