@@ -23,8 +23,6 @@
 // conv_epilogue.h.
 #ifndef BNN_BCONV_KERNEL_H
 #define BNN_BCONV_KERNEL_H
-#include <mutex>
-
 #include "bnn_internal.h"
 #include "conv_epilogue.h"
 #include "lds_dma.h"
@@ -806,16 +804,13 @@ bnn_status launch_geom(const uint32_t *in, const uint32_t *wt, const ConvGeom &g
                        hipStream_t s)
 {
     const unsigned blocks = (unsigned)(g.slots * g.n_co_tiles);
-    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel
-        // (callers on distinct threads may arrive here together; a failed attempt is reported to
-        // every caller of this kernel, a successful one is never repeated)
-        static std::once_flag once;
-        static hipError_t raise_err = hipSuccess;
-        std::call_once(once, [] {
-            raise_err = hipFuncSetAttribute((const void *)bconv_mfma<TM, TN, WPH, WDMA, LIN>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, MAX_SMEM);
+    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel and device
+        static PerDevice raised;
+        const hipError_t e = raised.run([] {
+            return hipFuncSetAttribute((const void *)bconv_mfma<TM, TN, WPH, WDMA, LIN>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, MAX_SMEM);
         });
-        if (raise_err != hipSuccess) return hip_result(raise_err);
+        if (e != hipSuccess) return hip_result(e);
     }
     hipLaunchKernelGGL((bconv_mfma<TM, TN, WPH, WDMA, LIN>), dim3(blocks), dim3(256), smem, s, in, wt, g, ep);
     return hip_result(hipGetLastError());

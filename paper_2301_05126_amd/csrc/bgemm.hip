@@ -20,8 +20,6 @@
 // All end in the same epilogue: optional int32 store, optional threshold/flip/bit-pack.  The two
 // small-problem kernels can also carry the model's last layer (TAIL): each block adds the share
 // of its 32-bit output words to the logits.
-#include <mutex>
-
 #include "bnn_internal.h"
 #include "conv_epilogue.h"
 #include "lds_dma.h"
@@ -756,14 +754,13 @@ bnn_status launch_mfma_out(const uint32_t *a, int64_t m, int64_t k, const uint32
     constexpr int RES = TM * TN >= 16 ? 1 : (TM * TN >= 4 ? 2 : 3);
     constexpr unsigned smem = (NBUF * 64 * (TM + TN) * KC + 4 * XW) * 4;
     static_assert(RES * smem <= 160 * 1024, "LDS of the resident blocks");
-    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel
-        static std::once_flag once;
-        static hipError_t raise_err = hipSuccess;
-        std::call_once(once, [] {
-            raise_err = hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel and device
+        static PerDevice raised;
+        const hipError_t e = raised.run([] {
+            return hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         });
-        if (raise_err != hipSuccess) return hip_result(raise_err);
+        if (e != hipSuccess) return hip_result(e);
     }
     // a whole number of blocks per XCD; those without a tile leave at once
     const unsigned blocks = 8u * (unsigned)ceil_div64(gw.tiles < 256 * RES ? gw.tiles : 256 * RES, 8);

@@ -214,16 +214,15 @@ namespace {
 // In host code the array's name is only a handle for the symbol lookup below, never an address:
 // each device holds its own copy at its own address, fetched once per device (with that device
 // current) and used from then on for everything the host does with the array's memory.
-constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mutex;
-void *scratch_ptr[MAX_DEVICES] = {};
+void *scratch_ptr[bnn::MAX_DEVICES] = {};
 
 bnn_status static_scratch_of_current_device(void **out)
 {
     int dev = -1;
     bnn_status st = bnn::hip_result(hipGetDevice(&dev));
     if (st != BNN_OK) return st;
-    if (dev < 0 || dev >= MAX_DEVICES) return BNN_ERR_UNSUPPORTED;
+    if (dev < 0 || dev >= bnn::MAX_DEVICES) return BNN_ERR_UNSUPPORTED;
     std::lock_guard<std::mutex> lock(scratch_mutex);
     if (!scratch_ptr[dev]) {
         void *p = nullptr;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "bnn.h"
 
 namespace bnn {
@@ -40,6 +42,32 @@ struct ClearArgs {
 
 // Records a HIP error for bnn_last_hip_error() and returns BNN_ERR_HIP, or BNN_OK.
 bnn_status hip_result(hipError_t e);
+
+// A kernel's attributes belong to the device that is current when they are set.  run() calls `set` once
+// for each device (callers on distinct threads may arrive together); what the call returned is
+// returned to every later caller on that device.
+constexpr int MAX_DEVICES = 64;
+class PerDevice {
+public:
+    template <typename F>
+    hipError_t run(int dev, F &&set)
+    {
+        if (dev < 0 || dev >= MAX_DEVICES) return set();
+        std::call_once(once_[dev], [&] { result_[dev] = set(); });
+        return result_[dev];
+    }
+    template <typename F>
+    hipError_t run(F &&set)
+    {
+        int dev = -1;
+        const hipError_t e = hipGetDevice(&dev);
+        return e != hipSuccess ? e : run(dev, set);
+    }
+
+private:
+    std::once_flag once_[MAX_DEVICES];
+    hipError_t result_[MAX_DEVICES] = {};
+};
 
 // Kernel launchers.  Arguments are already validated; they only pick a launch shape,
 // enqueue on `s` and report launch errors.

@@ -25,6 +25,20 @@ extern "C" int bnn_test_conv_binary_kernel_choice(int n, int h, int w, int c_in,
     return bnn::conv_binary_kernel_choice(n, h, w, c_in, c_out, tiles_only != 0);
 }
 
+// Runs the once-per-device helper behind the kernels' LDS opt-in over a list of device numbers, with a
+// setter that counts its calls per entry and fails on device `bad`; results[i] = what entry i got.
+extern "C" void bnn_test_per_device(const int *devs, int n, int bad, int *calls, int *results)
+{
+    bnn::PerDevice once;
+    for (int i = 0; i < n; ++i) {
+        calls[i] = 0;
+        results[i] = (int)once.run(devs[i], [&] {
+            ++calls[i];
+            return devs[i] == bad ? hipErrorInvalidValue : hipSuccess;
+        });
+    }
+}
+
 // Which kernel bnn_fc_binary runs a product on: 0 = m <= 8 rows, 1 = 32 x 32 tiles with K split over the
 // waves, 2 / 3 / 4 = persistent 64 x 64, 128 x 128, 256 x 256 tiles.  Host-only.
 extern "C" int bnn_test_fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, int raw, int packed)

@@ -201,6 +201,18 @@ def test_kernel_choice_of_the_benchmark_shapes(lib):
     assert conv_kernel_choice(4, 8, 8, 2048, 32) == -1       # more than 1024 channels: unsupported
 
 
+def test_lds_opt_in_is_per_device(lib):
+    # the limit of dynamic LDS is raised on each device that a kernel runs on, not only on the first;
+    # a failure is reported to every later call on its device; numbers past the table are not kept
+    from tests.gpu_util import hooks
+    devs = [0, 0, 1, 0, 3, 1, 3, 2, 64, 64, 63]
+    n = len(devs)
+    calls, results = (C.c_int * n)(), (C.c_int * n)()
+    hooks().bnn_test_per_device((C.c_int * n)(*devs), n, 3, calls, results)
+    assert list(calls) == [1, 0, 1, 0, 1, 0, 0, 1, 1, 1, 1]
+    assert [r != 0 for r in results] == [d == 3 for d in devs]
+
+
 def test_kernel_choice_of_products_with_many_columns(lib):
     # the number of columns does not take a product off the tile kernels
     from tests.gpu_util import FC_TILE_64, FC_TILE_128, FC_TILE_256, fc_kernel_choice

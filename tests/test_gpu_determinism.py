@@ -6,7 +6,8 @@ import torch
 
 import paper_2301_05126_amd as P
 import workloads as W
-from tests.gpu_util import DeviceModel, dev, fill_i32, require_gpu
+from tests.gpu_util import (FC_TILE_256, TILE_256x128, DeviceModel, conv_kernel_choice, dev, fc_kernel_choice,
+                            fill_i32, require_gpu)
 
 pytestmark = pytest.mark.gpu
 
@@ -91,3 +92,47 @@ def test_two_model_objects_on_two_streams_at_once(name, batch):
         torch.cuda.synchronize()
         for i in range(2):
             np.testing.assert_array_equal(dms[i].logits.cpu().numpy(), want[i], err_msg=f"stream {i}, repeat {rep}")
+
+
+# The first call of kernels with more than 64 KB of LDS in a process, made inside a graph capture (the
+# opt-in for that much LDS happens there too); replays compared with an FP32 product.
+FIRST_CALL_IN_CAPTURE = """
+import torch
+import paper_2301_05126_amd as P
+m, n, k = 4096, 4096, 1536
+g = torch.Generator(device="cuda").manual_seed(5)
+a, b = (torch.randint(-2**31, 2**31, (r, k // 32), dtype=torch.int32, generator=g, device="cuda") for r in (m, n))
+sh = torch.arange(32, dtype=torch.int32, device="cuda")
+one = lambda w: (2 * ((w[:, :, None] >> sh) & 1) - 1).reshape(w.shape[0], -1).float()
+want = (one(a) @ one(b).t().contiguous()).int()
+x, w = (torch.randint(-2**31, 2**31, (r, 8), dtype=torch.int32, generator=g, device="cuda") for r in (256 * 256, 256 * 9))
+xi, wi = one(x).reshape(256, 16, 16, 256), one(w).reshape(256, 3, 3, 256)
+pad = torch.nn.functional.pad(xi, (0, 0, 1, 1, 1, 1), value=-1.0)
+conv = sum(pad[:, i:i + 16, j:j + 16].reshape(-1, 256) @ wi[:, i, j].t().contiguous() for i in range(3) for j in range(3)).int()
+c = torch.zeros((m, n), dtype=torch.int32, device="cuda")
+d = torch.zeros((256 * 256, 256), dtype=torch.int32, device="cuda")
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    P.bnn_fc_binary(a, m, k, b, n, c_out=c)
+    P.bnn_conv_binary(x, 256, 16, 16, 256, w, 256, preact_out=d)
+for _ in range(3):
+    c.fill_(7)
+    d.fill_(7)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(c, want)
+    assert torch.equal(d, conv)
+print("first call in capture: ok")
+"""
+
+
+def test_first_call_inside_a_capture():
+    import os
+    import subprocess
+    import sys
+    assert fc_kernel_choice(4096, 4096, 1536) == FC_TILE_256                     # 144 KB
+    assert conv_kernel_choice(256, 16, 16, 256, 256) == TILE_256x128             # 69 KB
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FIRST_CALL_IN_CAPTURE], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "first call in capture: ok" in r.stdout, r.stdout + r.stderr
