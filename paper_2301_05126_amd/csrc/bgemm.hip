@@ -100,6 +100,14 @@ struct GemmWalk {
 // after, us: 16384^3 1518 / 1361, 8192^3 210 / 193, 4096^3 34.4 / 31.7 (a single round: 9 of its 32 us
 // are the stores), step output at 5000 x 5000 x 10000 194 / 107, 4096 x 1024 x 8192 19.3 / 14.7.
 //
+// The smaller tiles expand two (64 x 64) or one (128 x 128) words per MFMA and are bound by the vector ALU,
+// with one wave per SIMD also by what delays it: they make their operands from pairs of words, 5.5
+// vector instructions per word instead of 7, and the next chunk's words are read one step behind
+// the barrier (right behind it, a chunk took some 100 ticks longer at most alignments of the code).
+// us, words one by one and read at the barrier / now: 896 x 896, K = 16384 17.2 / 15.0 (step output 16.4 /
+// 14.3), 9 x 16384, K = 4096 6.1 / 5.6, 3000^3 21.8 / 20.8, 5000 x 5000, K = 1024 25.6 / 24.4.  Neither
+// changes the 256 x 256 tile, and eight buffers instead of four make the 64 x 64 tile slower.
+//
 // An LDS row is four 16-byte units; unit u of row r sits at position u ^ ((r >> 1) & 3), so that the
 // eight rows which one phase of a 16-byte read touches fall into distinct bank groups.  (A transfer
 // writes 1 KB linearly; which unit a lane fetches makes the arrangement.)  Rows past M or N and
@@ -119,6 +127,8 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                                                       int Kw, int K, GemmWalk gw, EpiArgs ep)
 {
     constexpr int BM = 64 * TM, BN = 64 * TN;     // 2 x 2 waves
+    // operands made from pairs of words: the 256 x 256 tile has no registers to spare for it
+    constexpr bool PAIR = TM * TN < 16;
     constexpr int IA = VEC == 4 ? TM : 4 * TM, IB = VEC == 4 ? TN : 4 * TN;   // transfers per wave and chunk
     constexpr int IPC = IA + IB;
     constexpr int ROWS_I = VEC == 4 ? 16 : 4;     // rows that one transfer fills
@@ -255,14 +265,20 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
         // operands of the current and the next step (FP4: the low four dwords of an MFMA operand)
         v4i a[2][TM], b[2][TN];
         auto operand = [](const v4i &x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; };
-        auto expand4 = [&](uint32_t w) {
-            const v8i e = expand_fp4(w, sgn, one);
-            return v4i{e[0], e[1], e[2], e[3]};
+        // words 2p and 2p + 1 of a group: the words of two consecutive steps (see shift_pair_half)
+        auto pair_of = [](const uint4 &v, int p) { return p == 0 ? make_uint2(v.x, v.y) : make_uint2(v.z, v.w); };
+        auto expand4 = [&](const uint4 &v) {
+            if (!PAIR) {
+                const v8i e = expand_fp4(v.x, sgn, one);
+                return v4i{e[0], e[1], e[2], e[3]};
+            }
+            const uint2 lo = expand_pair_half(pair_of(v, 0), 0, 0, sgn, one), hi = expand_pair_half(pair_of(v, 0), 0, 1, sgn, one);
+            return v4i{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
         };
 #pragma unroll
-        for (int i = 0; i < TM; ++i) a[0][i] = expand4(wa[0][i].x);
+        for (int i = 0; i < TM; ++i) a[0][i] = expand4(wa[0][i]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) b[0][j] = expand4(wb[0][j].x);
+        for (int j = 0; j < TN; ++j) b[0][j] = expand4(wb[0][j]);
 
         constexpr int NM = TM * TN, NW = TM + TN;
 #pragma unroll 1
@@ -285,27 +301,48 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                                  "s_waitcnt vmcnt(%1)\n"
                                  ".Lgemm_lax%=:\n\t"
                                  "s_barrier" ::"n"(YOUNGER + NST < 63 ? YOUNGER + NST : 63), "n"(YOUNGER), "s"(lax) : "memory", "scc");
+                uint2 pend[2 * NW];                       // shifted pairs awaiting their masks
 #pragma unroll
                 for (int k = 0; k < NM; ++k) {
                     const int i = k / TN, j = k % TN;
                     acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(b[cur][j]), operand(a[cur][i]),
                                                                                 acc[i][j], 4, 4, 0, 0, 0, 0);
-                    if (st == 0 || st == 4) {
+                    if (st == 0 || st == 5) {              // this chunk's second group, the next one's first
 #pragma unroll
                         for (int w = k * NW / NM; w < (k + 1) * NW / NM; ++w)
                             load_word(st == 0 ? buf : buf_n, st == 0 ? 1 : 0, w);
                     }
-                    if (st == 5) {
+                    if (st == 6) {
 #pragma unroll
                         for (int f = k * IPC / NM; f < (k + 1) * IPC / NM; ++f) fetch(f);
                     }
+                    if constexpr (PAIR) {
+                        // the next step's operands, two dwords at a time: a shift of a pair of words, and one
+                        // MFMA later (LAG) its masks, so that no instruction waits for the one before it
+                        constexpr int NIT = 2 * NW, LAG = NM > 1 ? 1 : 0;
 #pragma unroll
-                    for (int d = k * 4 * NW / NM; d < (k + 1) * 4 * NW / NM; ++d) {
-                        const int w = d >> 2, part = d & 3;
-                        if (w < TM) a[nxt][w][part] = (int)expand_part(word_of(wa[g1][w], q1), part, sgn, one);
-                        else b[nxt][w - TM][part] = (int)expand_part(word_of(wb[g1][w - TM], q1), part, sgn, one);
-                        // (used here, lest the next chunk's first operands be made after the last MFMA)
-                        if (st == 7 && part == 3) asm volatile("" ::"v"(w < TM ? a[nxt][w] : b[nxt][w - TM]));
+                        for (int t2 = 0; t2 < NIT; ++t2) {
+                            const int ks = t2 * (NM - LAG) / NIT;           // the MFMA that the shift follows
+                            const int w = t2 >> 1, dp = t2 & 1;
+                            if (ks == k) pend[t2] = shift_pair_half(pair_of(w < TM ? wa[g1][w] : wb[g1][w - TM], q1 >> 1), q1 & 1, dp);
+                            if (ks + LAG == k) {
+                                const uint2 e = mask_pair(pend[t2], sgn, one);
+                                v4i &o = w < TM ? a[nxt][w] : b[nxt][w - TM];
+                                o[2 * dp] = (int)e.x;
+                                o[2 * dp + 1] = (int)e.y;
+                                // (used here, lest the next chunk's first operands be made after the last MFMA)
+                                if (st == 7 && dp == 1) asm volatile("" ::"v"(o));
+                            }
+                        }
+                    } else {
+#pragma unroll
+                        for (int d = k * 4 * NW / NM; d < (k + 1) * 4 * NW / NM; ++d) {
+                            const int w = d >> 2, part = d & 3;
+                            if (w < TM) a[nxt][w][part] = (int)expand_part(word_of(wa[g1][w], q1), part, sgn, one);
+                            else b[nxt][w - TM][part] = (int)expand_part(word_of(wb[g1][w - TM], q1), part, sgn, one);
+                            // (used here, lest the next chunk's first operands be made after the last MFMA)
+                            if (st == 7 && part == 3) asm volatile("" ::"v"(w < TM ? a[nxt][w] : b[nxt][w - TM]));
+                        }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
