@@ -377,7 +377,11 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
             const int32_t *rp = Xw + sr * 32 + ((sq ^ sr) << 2);
             const unsigned col = (unsigned)(n0 + col0) + sq * 4u;            // of tile column 0
             unsigned at = (unsigned)(wm * TM * 32 + sr) * c_row + col * 4u;
-            const bool whole = (N & 3) == 0 || n0 + BN <= N;                // a quad is all inside or all outside
+            // quads of columns that are all inside or all outside.  A small tile that is its block's only one
+            // takes a lane per column where rows are no whole number of quads: its stores are not hidden
+            // behind another tile's chunks, and quads on 4-byte addresses drain slowly (2500 x 2501, K = 1000
+            // 10.75 us with quads, 10.18 so; 2000 x 2001, K = 300 9.33 / 8.64; 1500 x 1501, K = 300 7.23 / 7.28).
+            const bool whole = (N & 3) == 0 || (n0 + BN <= N && (TM * TN >= 16 || gw.tiles > (int)gridDim.x));
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -461,6 +465,16 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                                 if (gw.stream) __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 2);
                                 else __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 0);
                             }
+                    } else if constexpr (TM * TN < 16) {
+                        const unsigned cl = (unsigned)(n0 + col0) + j0 * 32 + l32;
+                        const unsigned al = (unsigned)(r0 + half) * c_row + cl * 4u;
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) {                    // rows 2k and 2k + 1, a lane per column
+                            const int row = 2 * k + half;
+                            const int v = Xw[row * 32 + (((l32 >> 2) ^ (row & 7)) << 2) + (l32 & 3)];
+                            __builtin_amdgcn_raw_buffer_store_b32(v, crs, (cl < (unsigned)N ? al : 0x80000000u) + 2 * k * c_row, 0, 0);
+                        }
+                        asm volatile("" ::: "memory");
                     } else {
 #pragma unroll
                         for (int j = 0; j < GJ; ++j)

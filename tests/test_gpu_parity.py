@@ -173,7 +173,7 @@ def test_fc_binary_raw_and_fused(m, n, k):
 # cache line, and on one; first the 256 x 256 tile, then 128 x 128, then 64 x 64.
 @pytest.mark.parametrize("m,n,k", [(4352, 4352, 512), (4097, 4352, 1024), (4200, 4401, 520), (4100, 4500, 1500),
                                    (2560, 4864, 256), (2500, 4801, 1100), (2561, 4610, 33), (900, 1000, 200),
-                                   (777, 1029, 1537)])
+                                   (777, 1029, 1537), (1700, 2051, 70), (1701, 2050, 1100)])
 def test_fc_binary_tile_rounds(m, n, k):
     print("fc rounds", m, n, k, flush=True)
     rng = rng_of(m + 2 * n + 3 * k)
