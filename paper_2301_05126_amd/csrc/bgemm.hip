@@ -120,8 +120,10 @@ struct GemmWalk {
 constexpr int KC = 16, NBUF = 4, XW = 32 * 32;
 
 // RAW / PACKED: which outputs the instance writes (one of the two in all but diagnostic calls).
-// FAR: raw sums whose rows are so long that 32-bit offsets do not reach over a tile's.
-template <int TM, int TN, int VEC, int OCC, bool RAW, bool PACKED, bool FAR>
+// STORE: how raw sums leave.  QUADS: 16-byte stores; FAR: the same where rows are so long that 32-bit
+// offsets do not reach over a tile's; LANES: 4-byte stores, a lane per column.
+enum { QUADS = 0, FAR = 1, LANES = 2 };
+template <int TM, int TN, int VEC, int OCC, bool RAW, bool PACKED, int STORE>
 __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restrict__ A,
                                                       const uint32_t *__restrict__ B, int64_t M, int64_t N,
                                                       int Kw, int K, GemmWalk gw, EpiArgs ep)
@@ -365,8 +367,12 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
             // accumulators (32 bytes to a row) take 308 us at 8192^3, 64 bytes to a row 212 us, this
             // 195 us.  The stores go through a buffer resource over the tile's rows of C, or (FAR) over
             // eight of them at a time: a row past M or a column past N addresses past its end and is dropped.
-            // Where not even eight rows fit, 64-bit addresses.  (FAR is apart: eight rows at a time always
-            // takes up to 7 % longer, and all three in one instance spill scalar registers.)
+            // Where not even eight rows fit, 64-bit addresses.  LANES: a small tile that is its block's only
+            // one, of a C whose rows are no whole number of quads: its stores are not hidden behind another
+            // tile's chunks, and quads on 4-byte addresses drain slowly (2500 x 2501, K = 1000 10.75 us with
+            // quads, 10.18 so; 2000 x 2001, K = 300 9.33 / 8.64; 1500 x 1501, K = 300 7.23 / 7.28).  (Instances of
+            // their own: eight rows at a time always takes up to 7 % longer, and a branch more in the
+            // epilogue cost the smallest products 3 %.)
             const unsigned c_row = (unsigned)N * 4u;
             const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
                 ep.preact + m0 * N, 0, (int)((unsigned)rows * c_row), 0x00020000);
@@ -377,11 +383,7 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
             const int32_t *rp = Xw + sr * 32 + ((sq ^ sr) << 2);
             const unsigned col = (unsigned)(n0 + col0) + sq * 4u;            // of tile column 0
             unsigned at = (unsigned)(wm * TM * 32 + sr) * c_row + col * 4u;
-            // quads of columns that are all inside or all outside.  A small tile that is its block's only one
-            // takes a lane per column where rows are no whole number of quads: its stores are not hidden
-            // behind another tile's chunks, and quads on 4-byte addresses drain slowly (2500 x 2501, K = 1000
-            // 10.75 us with quads, 10.18 so; 2000 x 2001, K = 300 9.33 / 8.64; 1500 x 1501, K = 300 7.23 / 7.28).
-            const bool whole = (N & 3) == 0 || (n0 + BN <= N && (TM * TN >= 16 || gw.tiles > (int)gridDim.x));
+            const bool whole = (N & 3) == 0 || n0 + BN <= N;                // a quad is all inside or all outside
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -403,7 +405,7 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                         __builtin_amdgcn_sched_barrier(0);      // one tile's registers at a time
                     }
                     const int r0 = wm * TM * 32 + i * 32;
-                    if constexpr (FAR) {
+                    if constexpr (STORE == FAR) {
                         if (gw.far == 1) {
                             const unsigned at8 = (unsigned)sr * c_row + col * 4u;
                             auto rows8 = [&](int k) {
@@ -455,6 +457,16 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                                     }
                                 }
                         }
+                    } else if constexpr (STORE == LANES) {
+                        const unsigned cl = (unsigned)(n0 + col0) + j0 * 32 + l32;
+                        const unsigned al = (unsigned)(r0 + half) * c_row + cl * 4u;
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) {                    // rows 2k and 2k + 1, a lane per column
+                            const int row = 2 * k + half;
+                            const int v = Xw[row * 32 + (((l32 >> 2) ^ (row & 7)) << 2) + (l32 & 3)];
+                            __builtin_amdgcn_raw_buffer_store_b32(v, crs, (cl < (unsigned)N ? al : 0x80000000u) + 2 * k * c_row, 0, 0);
+                        }
+                        asm volatile("" ::: "memory");
                     } else if (whole) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
@@ -465,16 +477,6 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                                 if (gw.stream) __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 2);
                                 else __builtin_amdgcn_raw_buffer_store_b128(x[j][k], crs, aj, 0, 0);
                             }
-                    } else if constexpr (TM * TN < 16) {
-                        const unsigned cl = (unsigned)(n0 + col0) + j0 * 32 + l32;
-                        const unsigned al = (unsigned)(r0 + half) * c_row + cl * 4u;
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {                    // rows 2k and 2k + 1, a lane per column
-                            const int row = 2 * k + half;
-                            const int v = Xw[row * 32 + (((l32 >> 2) ^ (row & 7)) << 2) + (l32 & 3)];
-                            __builtin_amdgcn_raw_buffer_store_b32(v, crs, (cl < (unsigned)N ? al : 0x80000000u) + 2 * k * c_row, 0, 0);
-                        }
-                        asm volatile("" ::: "memory");
                     } else {
 #pragma unroll
                         for (int j = 0; j < GJ; ++j)
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
                 }
                 at += 32 * c_row;
             }
-            after_stores = whole && !PACKED && (!FAR || gw.far == 1);
+            after_stores = whole && !PACKED && STORE != LANES && (STORE != FAR || gw.far == 1);
         }
         if constexpr (PACKED) {
             // thresholds through LDS (written and read by the same wave) into the accumulators' channel
@@ -793,29 +795,33 @@ __global__ __launch_bounds__(512) void bgemv_rows(const uint32_t *__restrict__ A
     }
 }
 
-template <int TM, int TN, int VEC, bool RAW, bool PACKED, bool FAR = false>
+template <int TM, int TN, int VEC, bool RAW, bool PACKED, int STORE = QUADS>
 bnn_status launch_mfma_out(const uint32_t *a, int64_t m, int64_t k, const uint32_t *b, int64_t n, int kw,
                            const GemmWalk &gw, const EpiArgs &ep, hipStream_t s)
 {
-    if constexpr (RAW && !FAR) {
-        if (gw.far) return launch_mfma_out<TM, TN, VEC, RAW, PACKED, true>(a, m, k, b, n, kw, gw, ep, s);
-    }
     // blocks per compute unit: the 256 x 256 tile fills the registers, the smaller ones the LDS
     constexpr int OCC = TM * TN >= 16 ? 1 : 2;
     constexpr int RES = TM * TN >= 16 ? 1 : (TM * TN >= 4 ? 2 : 3);
+    if constexpr (RAW && STORE == QUADS) {
+        if (gw.far) return launch_mfma_out<TM, TN, VEC, RAW, PACKED, FAR>(a, m, k, b, n, kw, gw, ep, s);
+        if constexpr (TM * TN < 16 && !PACKED) {
+            if ((n & 3) != 0 && gw.tiles <= 256 * RES)
+                return launch_mfma_out<TM, TN, VEC, RAW, PACKED, LANES>(a, m, k, b, n, kw, gw, ep, s);
+        }
+    }
     constexpr unsigned smem = (NBUF * 64 * (TM + TN) * KC + 4 * XW) * 4;
     static_assert(RES * smem <= 160 * 1024, "LDS of the resident blocks");
     if (smem > 64 * 1024) {          // above the default limit of dynamic LDS: opt in, once per kernel and device
         static PerDevice raised;
         const hipError_t e = raised.run([] {
-            return hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>,
+            return hipFuncSetAttribute((const void *)bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, STORE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         });
         if (e != hipSuccess) return hip_result(e);
     }
     // a whole number of blocks per XCD; those without a tile leave at once
     const unsigned blocks = 8u * (unsigned)ceil_div64(gw.tiles < 256 * RES ? gw.tiles : 256 * RES, 8);
-    hipLaunchKernelGGL((bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, FAR>), dim3(blocks), dim3(256), smem, s, a, b, m, n, kw,
+    hipLaunchKernelGGL((bgemm_mfma<TM, TN, VEC, OCC, RAW, PACKED, STORE>), dim3(blocks), dim3(256), smem, s, a, b, m, n, kw,
                        (int)k, gw, ep);
     return hip_result(hipGetLastError());
 }
