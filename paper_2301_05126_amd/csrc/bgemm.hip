@@ -847,8 +847,12 @@ bnn_status launch_mfma(const uint32_t *a, int64_t m, int64_t k, const uint32_t *
     gw.nbm = (int)nbm; gw.nbn = (int)nbn; gw.tiles = (int)tiles;
     // Streaming stores of raw sums, only of whole cache lines (6000 x 6001, K = 4096: 147 us with them, 81
     // without).  The 256 x 256 tile: where C is larger than the 256 MiB memory-side cache (12000 x 8000,
-    // K = 1024: 84.5 us with, 88.5 without; 8000 x 8000, K = 512: 54 with, 48 without).
-    gw.stream = (n & 31) == 0 && (TM * TN < 16 || m * n > (int64_t)1 << 26);
+    // K = 1024: 84.5 us with, 88.5 without; 8000 x 8000, K = 512: 54 with, 48 without).  Smaller tiles: near the
+    // size of that cache (5744 x 8352, K = 207 44.4 / 45.6), and in a single round, whose stores all leave at the
+    // end (3000 x 3072, K = 1024 10.4 / 11.9, 1597 x 4672, K = 896 8.8 / 10.2); between them the cache takes the
+    // stores faster (4096 x 4096, K = 512 16.2 / 14.9, 3020 x 8800, K = 156 26.5 / 23.6, 5657 x 6304, K = 782 35.5 / 33.3).
+    const int64_t large = TM * TN < 16 ? (int64_t)3 << 24 : (int64_t)1 << 26;
+    gw.stream = (n & 31) == 0 && (m * n > large || (TM * TN < 16 && tiles <= 768));
     gw.far = 64 * TM * n < (int64_t)1 << 29 ? 0 : (n < (int64_t)1 << 26 ? 1 : 2);
     if ((kw & 3) == 0) return launch_mfma_vec<TM, TN, 4>(a, m, k, b, n, kw, gw, ep, s);
     return launch_mfma_vec<TM, TN, 1>(a, m, k, b, n, kw, gw, ep, s);
@@ -902,11 +906,20 @@ bnn_status launch_gemv(const uint32_t *a, int64_t m, int64_t k, const uint32_t *
 
 }  // namespace
 
+// Microseconds per 512 bits of K that the busiest compute unit spends on m x n outputs in square tiles
+// of `tile`: each XCD takes an eighth of the tiles and has 32 compute units.  One 256 x 256 tile at a
+// time takes 2.06, two 128 x 128 tiles side by side 1.23, one alone 0.68 (fitted to 290 products).
+static double fc_tile_time(int64_t m, int64_t n, int tile)
+{
+    const int64_t tiles = ceil_div64(ceil_div64(m, tile) * ceil_div64(n, tile), 8);
+    if (tile == 256) return 2.06 * (double)ceil_div64(tiles, 32);
+    const int64_t full = tiles / 64, rest = tiles - full * 64;
+    return 1.23 * (double)full + (rest == 0 ? 0.0 : (rest <= 32 ? 0.68 : 1.23));
+}
+
 int fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, bool raw, bool packed)
 {
     if (m <= 8) return FC_GEMV;
-    // largest tile that still fills most of the 256 compute units
-    const int64_t want = 192;
     const bool both = raw && packed;                // diagnostic calls: the 256 x 256 tile would spill
     // Raw sums of millions of columns: there are tiles enough of any size, and the padding of the rows decides
     // (us, 256 x 256 / as chosen, n = 2^21: m = 9, K = 4096 847 / 374; m = 100, K = 64 390 / 180; m = 300, K = 4096
@@ -915,12 +928,23 @@ int fc_binary_kernel_choice(int64_t m, int64_t k, int64_t n, bool raw, bool pack
         if (m <= 64) return FC_TILE_64;
         return both || ceil_div64(m, 128) * 128 * 6 < ceil_div64(m, 256) * 256 * 5 ? FC_TILE_128 : FC_TILE_256;
     }
-    // Raw sums of a short K are mostly stores, which the 128 x 128 tile's two blocks per compute unit overlap
-    // with each other's multiplies (us, 256 x 256 / 128 x 128: 6000 x 6000, K = 640 41.1 / 31.1; 5000 x 5000, K =
-    // 1024 29.2 / 25.3; 4096 x 4096, K = 1024 18.7 / 18.1); an output around the size of the memory-side cache or
-    // larger favours the larger tile again (8000 x 8000, K = 512 56.3 / 60.1; 12000 x 8000, K = 1024 84 / 95).
-    const bool stores = raw && k <= 1024 && m * n <= (int64_t)3 << 24;
-    if (!both && !stores && ceil_div64(m, 256) * ceil_div64(n, 256) >= want) return FC_TILE_256;
+    // A tile has to fill most of the 256 compute units.
+    const int64_t want = 192;
+    if (!both && ceil_div64(m, 256) * ceil_div64(n, 256) >= want) {
+        // The 256 x 256 tile multiplies fastest; the 128 x 128 tile leaves less of the last round idle, and its
+        // two blocks per compute unit overlap one's stores with the other's multiplies.  us, 256 x 256 /
+        // 128 x 128.  Raw sums of a short K are mostly stores: 6000 x 6000, K = 640 41.1 / 30.6, 6607 x 5280, K =
+        // 1792 55.9 / 43.2, 8192 x 8192, K = 2048 87.4 / 74.2; where they are larger than the 256 MiB memory-side
+        // cache the larger tile: 9000 x 9000, K = 256 97.6 / 106.5, 12000 x 8000, K = 1024 84.7 / 94.1.  Otherwise
+        // the rounds decide: 7200 x 7200, K = 900 58.7 / 49.3, 8000 x 8000, K = 1024 60.0 / 61.7; with a tenth in
+        // favour of the smaller tile where stores are few: 1919 x 8521, K = 6272 with step 64.8 / 42.4, 9034 x 4320,
+        // K = 640 24.7 / 22.8, 4096 x 4096, K = 4096 23.9 / 26.3.
+        const bool brief = raw && k <= 1024;
+        if (raw && k <= 2048 && m * n <= (brief ? (int64_t)3 << 24 : (int64_t)1 << 26)) return FC_TILE_128;
+        if (brief && m * n > (int64_t)1 << 26) return FC_TILE_256;
+        if ((brief ? 1.0 : 1.1) * fc_tile_time(m, n, 256) <= fc_tile_time(m, n, 128)) return FC_TILE_256;
+        return FC_TILE_128;
+    }
     if (ceil_div64(m, 128) * ceil_div64(n, 128) >= want) return FC_TILE_128;
     // fewer than that many 64 x 64 tiles: 32 x 32 tiles with K split over the block's waves
     return fc_takes_small_kernel(m, n) ? FC_SMALL : FC_TILE_64;

@@ -226,6 +226,19 @@ def test_kernel_choice_of_products_with_many_columns(lib):
         assert fc_kernel_choice(64, n, 2048, True, False) == FC_TILE_64, n
 
 
+def test_kernel_choice_of_products(lib):
+    # short K, raw: mostly stores, on the 128 x 128 tile up to the size of the memory-side cache; otherwise
+    # the tile whose rounds fit better
+    from tests.gpu_util import FC_GEMV, FC_SMALL, FC_TILE_64, FC_TILE_128, FC_TILE_256, fc_kernel_choice
+    for m, n, k, raw, tile in [(7200, 7200, 900, True, FC_TILE_128), (8192, 8192, 2048, True, FC_TILE_128),
+                               (9000, 9000, 256, True, FC_TILE_256), (4096, 4096, 4096, True, FC_TILE_256),
+                               (16384, 16384, 16384, True, FC_TILE_256), (4096, 4096, 4096, False, FC_TILE_256),
+                               (1919, 8521, 6272, False, FC_TILE_128), (1919, 8521, 6272, True, FC_TILE_128),
+                               (1000, 2000, 3136, False, FC_TILE_64), (64, 512, 512, False, FC_SMALL),
+                               (8, 8192, 8192, True, FC_GEMV)]:
+        assert fc_kernel_choice(m, n, k, raw, not raw) == tile, (m, n, k, raw)
+
+
 @pytest.mark.parametrize("c_in", [257, 288, 352, 353, 384, 385, 480, 512, 513, 800, 992, 1024])
 @pytest.mark.parametrize("c_out", [1, 127, 128, 256, 300])
 def test_streamed_weights_stay_inside_the_tensor(lib, c_in, c_out):

@@ -95,6 +95,54 @@ def test_gemm_large_freivalds_rows_cols_samples(size, layer):
         assert c[i, j] == oracle.dot(a[i], b[j])
 
 
+def words_of(bits):
+    """bool [rows][n] on the GPU -> packed int32 words, in plain torch."""
+    rows, n = bits.shape
+    b = torch.nn.functional.pad(bits, (0, -n % 32)).reshape(rows, -1, 32).to(torch.int64)
+    v = (b << torch.arange(32, device=bits.device)).sum(-1)
+    return torch.where(v >= 2 ** 31, v - 2 ** 32, v).to(torch.int32)
+
+
+# The 256 x 256 tile at its edges: a single round and several, one to five K chunks of 512 bits, 16-byte
+# and 4-byte transfers, ragged last tiles; raw sums of one or two chunks run on it only where they are
+# larger than 2^26 (streaming stores where n is a multiple of 32).  Reference: the product of the unpacked
+# operands in FP32 (integers below 2^24: exact).
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("m,n,k,raw,step", [(3600, 3841, 2050, True, True), (4095, 8190, 2100, True, True),
+                                            (4096, 8192, 2176, True, True), (3590, 3840, 512, False, True),
+                                            (4095, 8190, 520, False, True), (4070, 8160, 1100, False, True),
+                                            (8200, 8224, 512, True, False), (8195, 8201, 1000, True, False),
+                                            (8193, 8224, 1000, True, False), (8200, 8224, 520, True, False)])
+def test_gemm_large_tile_rounds(m, n, k, raw, step):
+    print("large tile", m, n, k, raw, step, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m + 3 * n + 5 * k)
+    a, b = (2 * torch.randint(0, 2, (r, k), dtype=torch.int8, generator=g, device="cuda") - 1 for r in (m, n))
+    kw = (k + 31) // 32
+    ad, bd = fill_i32((m, kw), 0), fill_i32((n, kw), 0)
+    P.bnn_pack_bits(a, m, k, ad)
+    P.bnn_pack_bits(b, n, k, bd)
+    bt = b.float().t().contiguous()
+    want = torch.cat([(a[i:i + 1024].float() @ bt).int() for i in range(0, m, 1024)])
+    if raw:
+        assert fc_kernel_choice(m, n, k, True, False) == FC_TILE_256
+        c = fill_i32((m + 1, n), 123456)
+        P.bnn_fc_binary(ad, m, k, bd, n, c_out=c)
+        assert torch.equal(c[:m], want)
+        assert bool((c[m] == 123456).all())
+        del c
+    if step:
+        assert fc_kernel_choice(m, n, k, False, True) == FC_TILE_256
+        thr = want[m // 2].clone()                                          # ties
+        thr[::3] = torch.randint(-(k // 4), k // 4 + 1, thr[::3].shape, dtype=torch.int32, generator=g, device="cuda")
+        thr[-2:] = torch.tensor([2 ** 31 - 1, -2 ** 31], dtype=torch.int32)
+        flip = torch.randint(0, 2, (n,), dtype=torch.uint8, generator=g, device="cuda")
+        packed = fill_i32((m + 1, (n + 31) // 32), -1)
+        P.bnn_fc_binary(ad, m, k, bd, n, thr=thr, flip=flip, packed_out=packed)
+        for i in range(0, m, 1024):
+            assert torch.equal(packed[i:min(m, i + 1024)], words_of((want[i:i + 1024] > thr) ^ (flip != 0))), i
+        assert bool((packed[m] == -1).all())
+
+
 # Raw sums whose rows are so long that 32-bit offsets do not reach over a tile's (from 2^21, 2^22 and 2^23
 # columns on for tiles of 256, 128 and 64 rows; over eight rows from 2^26 on), with columns that end inside a quad and on one; the
 # reference is the product of the unpacked operands in FP32 (integers below 2^24: exact).

@@ -168,9 +168,10 @@ def test_fc_binary_raw_and_fused(m, n, k):
     np.testing.assert_array_equal(host_u32(packed2), pack_pm1(oracle.step(want, thr, None)))
 
 
-# The persistent tile kernels at their edges: several tiles per block, one to three K chunks of 512
-# bits, rows that are and are not whole 16-byte units, columns that end inside a quad, inside a
-# cache line, and on one; first the 256 x 256 tile, then 128 x 128, then 64 x 64.
+# The persistent tile kernels at their edges: one and several tiles per block, one to three K chunks of
+# 512 bits, rows that are and are not whole 16-byte units, columns that end inside a quad, inside a
+# cache line, and on one.  128 x 128 tiles, one product on the 256 x 256 tile (bits only; more of
+# those in the tests of large products), 64 x 64 tiles.
 @pytest.mark.parametrize("m,n,k", [(4352, 4352, 512), (4097, 4352, 1024), (4200, 4401, 520), (4100, 4500, 1500),
                                    (2560, 4864, 256), (2500, 4801, 1100), (2561, 4610, 33), (900, 1000, 200),
                                    (777, 1029, 1537), (1700, 2051, 70), (1701, 2050, 1100)])
