@@ -756,12 +756,14 @@ bool make_geom(int n, int h, int w, int c_in, int c_out, bool win, bool lin, Con
     return smem <= (size_t)MAX_SMEM;
 }
 
-// Estimated ticks of a layer's multiply phase on one tiling: how many tiles the busiest compute unit
+// Estimated ticks of a layer's multiply phase on one tiling: the tiles that the busiest compute unit
 // takes, times a tile's MFMAs per wave, times the ticks of an MFMA with the operand expansion of this
 // tile shape beside it (5.5 vector instructions per word and TM + TN words per TM * TN MFMAs).  Two
 // resident blocks hide each other's expansion up to 4 ticks per instruction (4 x 2: 33 ticks per MFMA
 // as measured; 1 x 1: 56), a block alone pays more (2 x 2: 41, 1 x 1: 69).  A tile's epilogue and its
-// barriers come on top, twice for a block alone.
+// barriers come on top, twice for a block alone; a last tile whose neighbour block has none is alone too
+// (counted as half of a pair, it sent 23 x 19 x 24, 64 -> 256 to the tiling that takes 6.2 us, not 5.5).
+// Before the first tile a block fetches its channels' weights, 100 ticks for 64 channels and two words.
 template <int TM, int TN, int WPH>
 double conv_cost(const ConvGeom &g, bool lin)
 {
@@ -769,16 +771,15 @@ double conv_cost(const ConvGeom &g, bool lin)
     constexpr double pair = 12 + 4 * ops > 33 ? 12 + 4 * ops : 33;
     constexpr double lone = 12 + 5.2 * ops > 33 ? 12 + 5.2 * ops : 33;
     constexpr double mfma = TM * TN * 9 * WPH;
+    constexpr double over = 300 + 150.0 * TM * TN;
+    constexpr double paired = mfma * pair + over, alone = mfma * lone + 2 * over;       // a tile's ticks
+    constexpr double prologue = 100.0 * TN * WPH;
     const int blocks = g.slots * g.n_co_tiles;
-    const int per_block = (g.n_ptiles + g.slots - 1) / g.slots;
-    const double over = 300 + 150.0 * TM * TN, addr = lin ? 1.08 : 1.0;
-    if (blocks <= 256) return addr * per_block * (mfma * lone + 2 * over);
-    // blocks b and b + 256 share a compute unit; the first `rest` slots have one tile more
+    const double addr = lin ? 1.08 : 1.0;
+    if (blocks <= 256) return prologue + addr * ((g.n_ptiles + g.slots - 1) / g.slots) * alone;
+    // blocks b and b + 256 share a compute unit; the first `rest` blocks have one tile more
     const int full = g.n_ptiles / g.slots, rest = (g.n_ptiles - full * g.slots) * g.n_co_tiles;
-    const int mates = blocks - 256;                          // compute units with two blocks
-    int most = full + (rest > 0);                            // tiles of the busiest compute unit
-    if (mates > 0) most = 2 * full + (rest > 256 ? 2 : (rest > 0 ? 1 : 0));
-    return addr * most * (mfma * pair + over);
+    return prologue + addr * (2 * full * paired + (rest > 256 ? 2 * paired : (rest > 0 ? alone : 0)));
 }
 
 // Rectangular or linear tiles, whichever cost less; working out a linear tile's addresses is some 8 %
@@ -857,10 +858,13 @@ namespace {
 // short for them to matter.)
 template <int WPH> constexpr bool narrow_tiles = WPH == 2 || WPH == 4 || WPH == 6;
 
-// Which block tile launch_wph takes: the one of least estimated cost.  The estimate is good to some
-// ten per cent (over 50 layers the tile it picks is the fastest one or within 5 % of it in all but
-// three), so the largest tile, which moves the least data, stays where it gives nearly every compute
-// unit two blocks unless another promises 15 % less.
+// Which block tile launch_wph takes: the one of least estimated cost.  Over 219 layers it takes 1.7 % more
+// than the fastest tile and tiling on average and 5 % more for 26 of them; furthest off are raw sums,
+// whose stores the estimate leaves out (127 x 26 x 26, 64 -> 171 78 us, 52.7 with 64 x 64), and kernels
+// that keep few MFMAs in flight (578 x 28 x 14, 384 -> 192 pooled 81 / 61 with 256 x 64, 1431 x 8 x 8, 192 -> 256
+// 29.1 / 24.7 with 128 x 128).  The largest tile, which moves the least data, stays where it gives nearly
+// every compute unit two blocks unless another promises 10 % less (without that 598 x 28 x 28, 64 -> 48
+// 21.3 -> 27.1, 305 x 21 x 21, 448 -> 149 66.6 -> 80.3).
 // us, largest / picked: 131 x 27 x 31, 256 -> 64 15.3 / 11.3 (256 x 64), 24 x 27 x 27, 400 -> 96
 // 19.6 / 14.3 (128 x 128), 100 x 16 x 16, 320 -> 320 23.8 / 17.0 (256 x 64), 64 x 8 x 8, 512 -> 512
 // 17.0 / 9.2 (64 x 64).
@@ -878,7 +882,7 @@ int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win)
     };
     int64_t items;
     const double big = cost_one<4, 2, WPH, WD>(n, h, w, c_in, c_out, win, &items);
-    take(3, items >= 384 ? 0.85 * big : big);
+    take(3, items >= 384 ? 0.9 * big : big);
     take(WD ? 2 : 1, cost_one<2, 2, WPH, WD>(n, h, w, c_in, c_out, win));
     if constexpr (narrow_tiles<WPH>) {
         take(4, cost_one<4, 1, WPH>(n, h, w, c_in, c_out, win));

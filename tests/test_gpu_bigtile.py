@@ -24,8 +24,8 @@ def _gpu():
 
 # (n, h = w, c_in, c_out): one shape per channel-word width of the big tile (2, 4, 8, 12, 16 and 32
 # words per pixel); the 8 x 8 shapes have four images per pixel tile and a ragged last tile
-BIG_TILE_SHAPES = [(512, 14, 64, 64), (131, 32, 128, 128), (512, 16, 256, 256), (1026, 8, 512, 512),
-                   (2050, 8, 1024, 128), (300, 16, 128, 256), (256, 16, 384, 256)]
+BIG_TILE_SHAPES = [(512, 14, 64, 64), (259, 32, 128, 128), (512, 16, 256, 256), (1026, 8, 512, 512),
+                   (2046, 8, 1024, 128), (400, 16, 128, 256), (256, 16, 384, 256)]
 
 
 @pytest.mark.timeout(600)
