@@ -467,6 +467,11 @@ void bconv_mfma(const uint32_t *__restrict__ in, const uint32_t *__restrict__ wt
     // The packed words of a tile go to one of two LDS output tiles and are copied to global
     // memory after the next tile's barrier, so the stores drain while the next tile is
     // multiplied and the block needs one barrier per tile.
+    // The tile loop starts 4 bytes behind a 32-byte boundary, whatever the code before it: where the layer's
+    // multiplies fit one or two rounds its speed depends on that (256 x 128 tile, four words per pixel,
+    // us at the eight places of a word in 32 bytes: 350 x 16 x 16, 128 -> 256 15.06 here, 15.13 .. 15.50
+    // elsewhere; at 1024 x 16 x 16, 128 -> 128 15.22 and 15.27 .. 15.65).
+    asm volatile(".p2align 5\n\t.fill 1, 4, 0xbf800000");        // s_nop 0
     int it = 0;
     for (int ptile = slot; ptile < g.n_ptiles; ptile += g.slots, ++it) {
         const int buf = g.dbuf ? (it & 1) : 0;
