@@ -53,7 +53,9 @@ def test_pack_bits_general_int8_values():
 # Rows that are no whole number of words: every byte alignment of a row start, tensors shorter than
 # one 16-byte load, rows around the block's span of 1024 half words (16 KB), more rows than a grid.
 @pytest.mark.parametrize("rows,k", [(1, 15), (5, 3), (16, 1), (1, 17), (2, 31), (3, 47), (9, 49), (1031, 33), (333, 95),
-                                    (7, 16351), (5, 16383), (3, 16417), (2, 40001), (70001, 129)])
+                                    (7, 16351), (5, 16383), (3, 16417), (2, 40001), (70001, 129),
+                                    (16, 2), (17, 1), (4, 4), (1, 16), (3, 16), (777, 15), (257, 5), (2100007, 3),
+                                    (2100003, 1)])
 def test_pack_bits_ragged_rows(rows, k):
     print("pack ragged", rows, k, flush=True)
     a = rng_of(rows + 7 * k).integers(-128, 128, size=(rows, k), dtype=np.int8)
