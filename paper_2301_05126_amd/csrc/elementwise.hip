@@ -127,8 +127,10 @@ __global__ void pack_bits_tiny(const int8_t *__restrict__ src, int rows, int k, 
 // and its window starts at input row 2q, column 2x: no other index is ever taken apart, and the step
 // to the thread's next pixel is a fixed (q, x) increment.  HBM-bound.  Before, an item's four 64-bit
 // divisions, eight flip bytes and eight thresholds were worked out and read anew for each pixel; us,
-// before / after (at 6 TB/s): 256 x 32 x 32 x 128 77 / 24 (23), with pooling 35 / 23 (23);
-// 1182 x 6 x 6 x 120 15.3 / 6.0 (3.5); 500 x 16 x 16 x 511 248 / 64 (45).
+// before / after (at 6 TB/s): 256 x 32 x 32 x 128 77 / 22 (23), with pooling 35 / 20 (23);
+// 1182 x 6 x 6 x 120 15.3 / 5.0 (3.5); 500 x 16 x 16 x 511 248 / 59 (45); 400 x 32 x 32 x 8 pooled 5.9 / 4.7 (2.2).
+// Small layers are a chain of memory round trips, so no load waits for another's value: whole groups
+// load without a branch, a short group's loads are guarded by its (uniform) size.
 struct StepGeom {
     int64_t pixels;                  // output pixels
     int w, c, wo, cwo, gb;
@@ -139,7 +141,8 @@ struct StepGeom {
     unsigned mg_wo;                  // magic_floor of wo
 };
 
-template <int POOL, int U>                                       // U: pixels of a thread in flight together
+// WHOLE: c is a multiple of eight, every group has eight channels or none.
+template <int POOL, int U, bool WHOLE>                           // U: pixels of a thread in flight together
 __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restrict__ x,
                                                         const int32_t *__restrict__ thr,
                                                         const uint8_t *__restrict__ flip, StepGeom g,
@@ -152,28 +155,31 @@ __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restric
     const int yb = (int)blockIdx.x / g.bx, xb = (int)blockIdx.x - yb * g.bx;
     const int grp = yb * 256 + (t - slot * g.gb);
     if (slot >= ppb) return;                                     // (whole quads of lanes: gb is a multiple of 4)
-    const int c0 = grp * 8;
-    const int nc = g.c - c0 < 8 ? g.c - c0 : 8;                  // channels of the group that exist (may be <= 0)
     if (grp >= g.cwo * 4) return;                                // (whole quads again)
+    const int nc = g.c - grp * 8 < 8 ? g.c - grp * 8 : 8;        // channels of the group that exist (may be <= 0)
+    // (WHOLE: a group without channels reads the first one's and drops the result, no branch around its loads)
+    const int c0 = WHOLE && nc <= 0 ? 0 : grp * 8;
+    const int ns = g.c & 7;                                      // channels of the short group
+    const unsigned valid = nc >= 8 ? 0xffu : (nc > 0 ? (1u << nc) - 1u : 0u);
     // thresholds and flips: three wide loads for a whole group (sixteen narrow gathers per thread made
-    // the address unit the bound of small layers); channels that do not exist get a threshold that is
-    // never exceeded
-    int tv[8];
-    unsigned fm = 0;
-    if (nc == 8) {
+    // the address unit the bound of small layers)
+    int tv[8] = {};
+    uint64_t fl = 0;                                             // flip bytes
+    if (WHOLE || nc >= 8) {
         const int4 a = *reinterpret_cast<const int4 *>(thr + c0), b = *reinterpret_cast<const int4 *>(thr + c0 + 4);
-        uint64_t fl = 0;
         if (flip) __builtin_memcpy(&fl, flip + c0, 8);
         tv[0] = a.x; tv[1] = a.y; tv[2] = a.z; tv[3] = a.w;
         tv[4] = b.x; tv[5] = b.y; tv[6] = b.z; tv[7] = b.w;
+    } else if (nc > 0) {
+        uint8_t f[8] = {};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) fm |= ((fl >> (8 * j)) & 0xff ? 1u : 0u) << j;
-    } else {
+        for (int j = 0; j < 7; ++j)
+            if (j < ns) {
+                tv[j] = thr[c0 + j];
+                if (flip) f[j] = flip[c0 + j];
+            }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            tv[j] = j < nc ? thr[c0 + j] : INT32_MAX;
-            if (flip && j < nc && flip[c0 + j]) fm |= 1u << j;
-        }
+        for (int j = 0; j < 7; ++j) fl |= (uint64_t)f[j] << (8 * j);
     }
     int64_t p = (int64_t)xb * ppb + slot;
     const int64_t stride = (int64_t)g.bx * ppb;
@@ -184,15 +190,17 @@ __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restric
         xo = (int)(p - q * g.wo);
     }
     auto load8 = [&](const int32_t *src, int (&v)[8]) {
-        if (nc == 8) {
+        if (WHOLE || nc >= 8) {
             const uint4 a = load16_unaligned(src), b = load16_unaligned(src + 4);
             v[0] = (int)a.x; v[1] = (int)a.y; v[2] = (int)a.z; v[3] = (int)a.w;
             v[4] = (int)b.x; v[5] = (int)b.y; v[6] = (int)b.z; v[7] = (int)b.w;
-        } else {
+        } else if (nc > 0) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = j < nc ? src[j] : INT32_MIN;
+            for (int j = 0; j < 7; ++j)
+                if (j < ns) v[j] = src[j];
         }
     };
+    unsigned fm = 0;                                             // flip bits
     auto step8 = [&](const int (&v)[8]) {
         unsigned b = 0;
 #pragma unroll
@@ -200,7 +208,7 @@ __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restric
         return b ^ fm;
     };
     for (; p < g.pixels; p += stride * U) {
-        int v[U][WIN][8];
+        int v[U][WIN][8] = {};
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (POOL == 1) {
@@ -215,6 +223,11 @@ __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restric
                 load8(src + (int64_t)(g.w + 1) * g.c, v[u][3 % WIN]);
             }
         }
+        // (the flip bits are put together behind the pixels' loads, lest those wait for the flips)
+        asm volatile("" : "+v"(fl));
+        fm = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fm |= ((fl >> (8 * j)) & 0xff ? 1u : 0u) << j;
         if (POOL == 2) {
             xo += g.step_x;
             q += g.step_q;
@@ -235,7 +248,7 @@ __global__ __launch_bounds__(256) void step_pool_kernel(const int32_t *__restric
             } else {
                 byte = step8(v[u][0]) | step8(v[u][1 % WIN]) | step8(v[u][2 % WIN]) | step8(v[u][3 % WIN]);
             }
-            unsigned word = byte << (8 * (t & 3));
+            unsigned word = (byte & valid) << (8 * (t & 3));
             word |= __shfl_xor(word, 1);
             word |= __shfl_xor(word, 2);
             const int64_t pu = p + u * stride;
@@ -305,9 +318,15 @@ bnn_status launch_threshold_sign_maxpool(const int32_t *x, int n, int h, int w, 
     g.bx = (int)bx;
     g.mg_wo = magic_floor(g.wo);
     const dim3 grid((unsigned)(bx * by));
-    if (four) hipLaunchKernelGGL((step_pool_kernel<1, 4>), grid, dim3(256), 0, s, x, thr, flip, g, out);
-    else if (pool == 1) hipLaunchKernelGGL((step_pool_kernel<1, 1>), grid, dim3(256), 0, s, x, thr, flip, g, out);
-    else hipLaunchKernelGGL((step_pool_kernel<2, 1>), grid, dim3(256), 0, s, x, thr, flip, g, out);
+#define BNN_STEP(POOL, U)                                                                                      \
+    do {                                                                                                       \
+        if ((c & 7) == 0) hipLaunchKernelGGL((step_pool_kernel<POOL, U, true>), grid, dim3(256), 0, s, x, thr, flip, g, out); \
+        else hipLaunchKernelGGL((step_pool_kernel<POOL, U, false>), grid, dim3(256), 0, s, x, thr, flip, g, out); \
+    } while (0)
+    if (four) BNN_STEP(1, 4);
+    else if (pool == 1) BNN_STEP(1, 1);
+    else BNN_STEP(2, 1);
+#undef BNN_STEP
     return hip_result(hipGetLastError());
 }
 

@@ -113,7 +113,8 @@ def test_threshold_sign_maxpool(n, h, w, c, pool, use_flip):
 # end inside a quad of lanes, more groups than a block has threads, extreme sums and thresholds, and
 # flips at an odd address.
 @pytest.mark.parametrize("n,h,w,c", [(1, 2, 2, 1), (3, 6, 10, 9), (5, 14, 18, 72), (40, 30, 26, 100), (300, 16, 16, 33),
-                                     (130, 32, 32, 64), (2, 4, 6, 2047), (2, 2, 4, 2056), (1, 2, 2, 5000)])
+                                     (130, 32, 32, 64), (2, 4, 6, 2047), (2, 2, 4, 2056), (1, 2, 2, 5000),
+                                     (60, 8, 8, 7), (33, 6, 4, 8), (700, 16, 16, 3), (17, 10, 10, 13), (5, 4, 4, 24)])
 @pytest.mark.parametrize("pool,pool_first", [(1, 0), (2, 0), (2, 1)])
 def test_threshold_sign_maxpool_groups(n, h, w, c, pool, pool_first):
     print("step groups", n, h, w, c, pool, pool_first, flush=True)
