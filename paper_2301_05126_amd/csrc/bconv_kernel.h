@@ -836,14 +836,13 @@ bnn_status launch_one(const uint32_t *in, const uint32_t *wt, int n, int h, int 
 }
 
 // Estimated cost of a (64*TM pixels) x (64*TN channels) block tile, or a negative number if it does
-// not fit LDS.  `items`: its work items (pixel tiles x channel tiles).
+// not fit LDS.  `items`: its work items (pixel tiles x channel tiles).  *lin: its tiles are linear.
 template <int TM, int TN, int WPH, bool WDMA = false>
-double cost_one(int n, int h, int w, int c_in, int c_out, bool win, int64_t *items = nullptr)
+double cost_one(int n, int h, int w, int c_in, int c_out, bool win, bool *lin, int64_t *items = nullptr)
 {
     ConvGeom g;
     size_t smem;
-    bool lin;
-    const double cost = pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, g, smem, &lin);
+    const double cost = pick_geom<TM, TN, WPH, WDMA>(n, h, w, c_in, c_out, win, g, smem, lin);
     if (items) *items = cost < 0 ? 0 : (int64_t)g.n_ptiles * g.n_co_tiles;
     return cost;
 }
@@ -874,26 +873,28 @@ template <int WPH> constexpr bool narrow_tiles = WPH == 2 || WPH == 4 || WPH == 
 // 19.6 / 14.3 (128 x 128), 100 x 16 x 16, 320 -> 320 23.8 / 17.0 (256 x 64), 64 x 8 x 8, 512 -> 512
 // 17.0 / 9.2 (64 x 64).
 // 3: 256 x 128, 2: 128 x 128 with streamed weights, 1: 128 x 128, 4: 256 x 64, 5: 128 x 64,
-// 0: 64 x 64.  win: a pooled layer (its tiles are made of 2x2 windows).
+// 0: 64 x 64.  win: a pooled layer (its tiles are made of 2x2 windows).  *raster: linear tiles.
 template <int WPH>
-int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win)
+int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win, bool *raster = nullptr)
 {
     // the larger tiles keep their weights resident (WPH <= 4) or stream them by DMA
     constexpr bool WD = WPH >= 6;
     double best = -1;
     int choice = 0;
+    bool lin = false, best_lin = false;
     auto take = [&](int c, double cost) {
-        if (cost >= 0 && (best < 0 || cost < best)) { best = cost; choice = c; }
+        if (cost >= 0 && (best < 0 || cost < best)) { best = cost; choice = c; best_lin = lin; }
     };
     int64_t items;
-    const double big = cost_one<4, 2, WPH, WD>(n, h, w, c_in, c_out, win, &items);
+    const double big = cost_one<4, 2, WPH, WD>(n, h, w, c_in, c_out, win, &lin, &items);
     take(3, items >= 384 ? 0.9 * big : big);
-    take(WD ? 2 : 1, cost_one<2, 2, WPH, WD>(n, h, w, c_in, c_out, win));
+    take(WD ? 2 : 1, cost_one<2, 2, WPH, WD>(n, h, w, c_in, c_out, win, &lin));
     if constexpr (narrow_tiles<WPH>) {
-        take(4, cost_one<4, 1, WPH>(n, h, w, c_in, c_out, win));
-        take(5, cost_one<2, 1, WPH>(n, h, w, c_in, c_out, win));
+        take(4, cost_one<4, 1, WPH>(n, h, w, c_in, c_out, win, &lin));
+        take(5, cost_one<2, 1, WPH>(n, h, w, c_in, c_out, win, &lin));
     }
-    take(0, cost_one<1, 1, WPH>(n, h, w, c_in, c_out, win));
+    take(0, cost_one<1, 1, WPH>(n, h, w, c_in, c_out, win, &lin));
+    if (raster) *raster = best_lin;
     return choice;
 }
 

@@ -56,7 +56,7 @@ def hooks():
         _hooks = C.CDLL(path)
         _hooks.bnn_test_conv_binary_tiles.argtypes = api._lib.bnn_conv_binary.argtypes
         _hooks.bnn_test_conv_binary_tiles.restype = C.c_int
-        _hooks.bnn_test_conv_binary_kernel_choice.argtypes = [C.c_int] * 6
+        _hooks.bnn_test_conv_binary_kernel_choice.argtypes = [C.c_int] * 7 + [C.POINTER(C.c_int)]
         _hooks.bnn_test_conv_binary_kernel_choice.restype = C.c_int
         _hooks.bnn_test_fc_binary_kernel_choice.argtypes = [C.c_int64] * 3 + [C.c_int] * 2
         _hooks.bnn_test_fc_binary_kernel_choice.restype = C.c_int
@@ -76,11 +76,22 @@ def conv_binary_tiles(inp, n, h, w, c_in, wt, c_out, thr=None, flip=None, pool=1
 
 
 KERNEL_SMALL, TILE_256x128, TILE_128x128_STREAMED, TILE_128x128, TILE_64x64 = 10, 3, 2, 1, 0
+TILE_256x64, TILE_128x64 = 4, 5
 
 
-def conv_kernel_choice(n, h, w, c_in, c_out, tiles_only=False):
-    """Which kernel a binary convolution of this shape runs on (host-side query, no GPU work)."""
-    return hooks().bnn_test_conv_binary_kernel_choice(n, h, w, c_in, c_out, 1 if tiles_only else 0)
+def conv_kernel_tiling(n, h, w, c_in, c_out, pool=1, tiles_only=False):
+    """(kernel, raster order) that a binary convolution of this shape runs on (host-side query, no GPU
+    work); a pooled layer may differ from an unpooled one."""
+    import ctypes as C
+    raster = C.c_int(-1)
+    choice = hooks().bnn_test_conv_binary_kernel_choice(n, h, w, c_in, c_out, pool, 1 if tiles_only else 0,
+                                                        C.byref(raster))
+    return choice, bool(raster.value)
+
+
+def conv_kernel_choice(n, h, w, c_in, c_out, tiles_only=False, pool=1):
+    """The kernel alone."""
+    return conv_kernel_tiling(n, h, w, c_in, c_out, pool, tiles_only)[0]
 
 
 def conv_weight_reads(c_in, c_out):

@@ -8,9 +8,9 @@ import torch
 
 import oracle
 import paper_2301_05126_amd as P
-from tests.gpu_util import (TILE_256x128, conv_kernel_choice, dev, fill_i32, host_u32, require_gpu)
+from tests.gpu_util import (TILE_256x128, conv_kernel_tiling, dev, fill_i32, host_u32, require_gpu)
 from tests.helpers import pack_pm1, unpack_words
-from tests.test_gpu_parity import extreme_thresholds
+from tests.test_gpu_parity import check_conv_all_forms, extreme_thresholds
 
 pytestmark = pytest.mark.gpu
 
@@ -31,7 +31,7 @@ BIG_TILE_SHAPES = [(512, 14, 64, 64), (259, 32, 128, 128), (512, 16, 256, 256), 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("n,hw,ci,co", BIG_TILE_SHAPES)
 def test_big_tile_full_oracle_all_epilogues(n, hw, ci, co):
-    assert conv_kernel_choice(n, hw, hw, ci, co) == TILE_256x128
+    assert conv_kernel_tiling(n, hw, hw, ci, co) == conv_kernel_tiling(n, hw, hw, ci, co, 2) == (TILE_256x128, False)
     print(f"big tile {n}x{hw}x{hw} {ci}->{co}: drawing", flush=True)
     rng = np.random.default_rng(n * 7 + hw * 3 + ci + co)
     cw = ci // 32
@@ -72,3 +72,17 @@ def test_big_tile_full_oracle_all_epilogues(n, hw, ci, co):
     pooled = fill_i32((n, hw // 2, hw // 2, co // 32), -1)
     P.bnn_conv_binary(xd, n, hw, hw, ci, wd, co, thr=td, flip=fd, pool=2, pool_first=1, packed_out=pooled)
     np.testing.assert_array_equal(host_u32(pooled), pack_pm1(oracle.step(oracle.maxpool2(want), thr, flip)))
+
+
+# The same tile over ragged images and channels, rectangles and raster order: every channel-word width
+# that takes it, pooled where the sizes are even.
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("n,h,w,ci,co,raster", [
+    (113, 30, 30, 40, 44, False), (207, 11, 15, 40, 130, False), (1119, 4, 26, 64, 33, True), (214, 23, 24, 40, 40, True),
+    (924, 6, 6, 99, 201, False), (117, 25, 24, 128, 68, False), (129, 20, 20, 99, 139, True), (102, 24, 21, 99, 132, True),
+    (877, 28, 4, 130, 68, False), (909, 7, 11, 130, 83, False), (503, 10, 10, 130, 131, True), (1115, 7, 13, 130, 68, True),
+    (959, 4, 12, 288, 132, False), (224, 12, 25, 288, 66, False), (617, 20, 4, 288, 130, True), (1114, 9, 5, 288, 137, True),
+    (100, 14, 30, 400, 143, False), (859, 7, 7, 400, 140, False), (89, 24, 24, 400, 145, True), (350, 22, 13, 400, 67, True),
+    (454, 25, 6, 640, 66, False)])
+def test_big_tile_ragged_images(n, h, w, ci, co, raster):
+    check_conv_all_forms(n, h, w, ci, co, TILE_256x128, raster)

@@ -143,6 +143,40 @@ def test_gemm_large_tile_rounds(m, n, k, raw, step):
         assert bool((packed[m] == -1).all())
 
 
+# The largest K of the matrix-core path, where T - x of the step no longer fits 24 bits and its sign has to
+# decide alone: row i of A is +1 in its first p_i places, row j of B in its first q_j, so that their product
+# is K - 2 |p_i - q_j|.
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("m,n,tile", [(896, 890, FC_TILE_64), (1700, 1790, FC_TILE_128), (3500, 3584, FC_TILE_256)])
+def test_gemm_largest_k(m, n, tile):
+    k = (1 << 24) - 2048
+    assert fc_kernel_choice(m, n, k, False, True) == tile
+    print("largest K", m, n, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+
+    def rows(r):
+        ends = torch.randint(0, k + 1, (r,), dtype=torch.int64, generator=g, device="cuda")
+        ends[:4] = torch.tensor([0, k, 1, k - 1])
+        first = torch.arange(0, k, 32, dtype=torch.int64, device="cuda")
+        w = torch.empty((r, k // 32), dtype=torch.int32, device="cuda")
+        for i in range(0, r, 32):
+            c = (ends[i:i + 32, None] - first).clamp_(0, 32)
+            v = (1 << c) - 1
+            w[i:i + 32] = torch.where(v >= 2 ** 31, v - 2 ** 32, v).to(torch.int32)
+        return ends, w
+    (p, a), (q, b) = rows(m), rows(n)
+    want = (k - 2 * (p[:, None] - q).abs()).to(torch.int32)
+    c = fill_i32((m, n), 7)
+    P.bnn_fc_binary(a, m, k, b, n, c_out=c)
+    assert torch.equal(c, want)
+    lim = torch.tensor([k, k - 1, -k, -k - 1, k + 1, 2 ** 31 - 1, -2 ** 31, 0], dtype=torch.int32, device="cuda")
+    thr = torch.cat([lim, lim, lim, lim, lim, lim, lim, lim, want[m // 2, 64:]])            # extremes, then ties
+    thr[65::3] -= 1
+    packed = fill_i32((m, (n + 31) // 32), -1)
+    P.bnn_fc_binary(a, m, k, b, n, thr=thr, packed_out=packed)
+    assert torch.equal(packed, words_of(want > thr))
+
+
 # Raw sums whose rows are so long that 32-bit offsets do not reach over a tile's (from 2^21, 2^22 and 2^23
 # columns on for tiles of 256, 128 and 64 rows; over eight rows from 2^26 on), with columns that end inside a quad and on one; the
 # reference is the product of the unpacked operands in FP32 (integers below 2^24: exact).

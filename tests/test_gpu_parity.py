@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2301_05126_amd as P
 import workloads as W
-from tests.gpu_util import (DEV, DeviceModel, conv_binary_tiles, conv_kernel_choice, dev, empty_i32, fill_i32, host_u32,
+from tests.gpu_util import (DEV, TILE_64x64, DeviceModel, conv_binary_tiles, conv_kernel_tiling, dev, empty_i32, fill_i32, host_u32,
                             pack_on_gpu, require_gpu)
 from tests.helpers import pack_pm1
 
@@ -342,13 +342,25 @@ def test_conv_first_raster_tiles(n, h, w, ci, co, kh, kw, pad, padv):
 
 # Images whose sizes leave rectangular pixel tiles half empty, in batches large enough for the tile
 # kernels to take tiles in raster order instead: every channel width, resident and streamed weights,
-# the three block tiles, windows and pixels, tiles that span many images or part of a row.
+# 128 x 128 and 64 x 64 block tiles (256 x 128: with the other large shapes), windows and pixels, tiles that
+# span many images or part of a row.
 @pytest.mark.parametrize("n,h,w,ci,co", [(200, 17, 17, 224, 96), (1137, 7, 7, 320, 72), (300, 21, 21, 64, 40),
                                          (600, 10, 10, 128, 128), (2100, 6, 6, 512, 128), (520, 3, 3, 1024, 2048),
-                                         (9000, 3, 3, 32, 32), (100, 9, 9, 160, 64), (40, 20, 100, 64, 33),
+                                         (9000, 3, 3, 32, 32), (100, 9, 9, 160, 64), (60, 10, 100, 64, 33),
+                                         (33, 20, 90, 64, 65),
                                          (130, 18, 34, 99, 70)])
 def test_conv_binary_raster_tiles(n, h, w, ci, co):
-    print("conv raster", n, h, w, ci, co, flush=True)
+    check_conv_all_forms(n, h, w, ci, co, raster=True)
+
+
+def check_conv_all_forms(n, h, w, ci, co, tile=None, raster=None):
+    """Raw sums, step, step + pool and pool + step of a binary convolution against the full oracle; the
+    block tile and the order of its tiles are those named, for pooled forms too."""
+    print("conv forms", n, h, w, ci, co, flush=True)
+    for pool in (1, 2) if h % 2 == 0 and w % 2 == 0 else (1,):
+        got = conv_kernel_tiling(n, h, w, ci, co, pool)
+        assert tile is None or got[0] == tile, (pool, got)
+        assert raster is None or got[1] == raster, (pool, got)
     rng = rng_of(n + 3 * h + 5 * w + 7 * ci + co)
     x, wt = pm1(rng, (n, h, w, ci)), pm1(rng, (co, 3, 3, ci))
     want = oracle.conv2d(x, wt, 1, -1)
@@ -375,15 +387,18 @@ def test_conv_binary_raster_tiles(n, h, w, ci, co):
         np.testing.assert_array_equal(raw[:n].cpu().numpy(), want)
 
 
+def test_conv_binary_wide_images_in_rectangles():
+    check_conv_all_forms(40, 20, 100, 64, 33, TILE_64x64, False)
+
+
 # The 64-channel tiles of 256 (4) and 128 (5) pixels: each channel width that has them, at its ends;
 # one channel group, a ragged last one, several; rectangles and raster order.
-@pytest.mark.parametrize("n,h,w,ci,co,tile", [(1000, 10, 10, 100, 33, 4), (200, 14, 14, 65, 33, 5),
-                                              (64, 14, 14, 128, 129, 5), (100, 32, 32, 160, 33, 4),
-                                              (1000, 9, 9, 256, 33, 5), (100, 16, 16, 257, 320, 4),
-                                              (100, 32, 32, 384, 33, 4), (200, 16, 16, 384, 33, 5)])
-def test_conv_binary_narrow_tiles(n, h, w, ci, co, tile):
-    assert conv_kernel_choice(n, h, w, ci, co) == tile
-    test_conv_binary_raster_tiles(n, h, w, ci, co)
+@pytest.mark.parametrize("n,h,w,ci,co,tile,raster", [(1000, 10, 10, 100, 33, 4, True), (200, 14, 14, 65, 33, 5, False),
+                                                     (64, 14, 14, 128, 129, 5, False), (100, 32, 32, 160, 33, 4, False),
+                                                     (1000, 9, 9, 256, 33, 5, True), (100, 16, 16, 257, 320, 4, False),
+                                                     (100, 32, 32, 384, 33, 4, False), (200, 16, 16, 384, 33, 5, False)])
+def test_conv_binary_narrow_tiles(n, h, w, ci, co, tile, raster):
+    check_conv_all_forms(n, h, w, ci, co, tile, raster)
 
 
 # ------------------------------------------------------------------- conv_first_int8
