@@ -99,7 +99,7 @@ def test_two_model_objects_on_two_streams_at_once(name, batch):
 FIRST_CALL_IN_CAPTURE = """
 import torch
 import paper_2301_05126_amd as P
-m, n, k = 4096, 4096, 1536
+m, n, k = 4096, 4096, 2176
 g = torch.Generator(device="cuda").manual_seed(5)
 a, b = (torch.randint(-2**31, 2**31, (r, k // 32), dtype=torch.int32, generator=g, device="cuda") for r in (m, n))
 sh = torch.arange(32, dtype=torch.int32, device="cuda")
@@ -131,7 +131,7 @@ def test_first_call_inside_a_capture():
     import os
     import subprocess
     import sys
-    assert fc_kernel_choice(4096, 4096, 1536) == FC_TILE_256                     # 144 KB
+    assert fc_kernel_choice(4096, 4096, 2176) == FC_TILE_256                     # 144 KB
     assert conv_kernel_choice(256, 16, 16, 256, 256) == TILE_256x128             # 69 KB
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", FIRST_CALL_IN_CAPTURE], cwd=root, capture_output=True, text=True, timeout=100)
