@@ -96,9 +96,10 @@ struct GemmWalk {
 // the 32 that a lone wave reaches with its operands in registers (46 with two barriers per chunk
 // and staging through registers), and the power limit, which holds the clock at 1.9 GHz; then the
 // stores of raw sums, 256 KB per tile and compute unit, in which the matrix pipe idles (9.4 us
-// where all compute units store at once, the chip's write bandwidth; 5.7 us otherwise).  Before and
-// after, us: 16384^3 1518 / 1361, 8192^3 210 / 193, 4096^3 34.4 / 31.7 (a single round: 9 of its 32 us
-// are the stores), step output at 5000 x 5000 x 10000 194 / 107, 4096 x 1024 x 8192 19.3 / 14.7.
+// where all compute units store at once, the chip's write bandwidth; 5.7 us otherwise).  One block per
+// tile with staging through registers / now, us: 16384^3 1518 / 1352, 8192^3 210 / 189, 4096^3 35.7 / 33.3 (a
+// single round: 9 of its 33 us are the stores; kernel traces, two cards), step output at 5000 x 5000 x
+// 10000 193 / 107, 4096 x 1024 x 8192 19.1 / 14.1.
 //
 // The smaller tiles expand two (64 x 64) or one (128 x 128) words per MFMA and are bound by the vector ALU,
 // with one wave per SIMD also by what delays it: they make their operands from pairs of words, 5.5
@@ -364,9 +365,10 @@ __global__ __launch_bounds__(256, OCC) void bgemm_mfma(const uint32_t *__restric
             // eight rows of 128 contiguous bytes: a lane writes its row's four quads of columns (quad c of
             // row r at position c ^ (r % 8): no bank conflicts either way) and reads quad lane % 8 of
             // rows lane / 8 + 8k.  Whole cache lines matter: quads stored as they come out of the
-            // accumulators (32 bytes to a row) take 308 us at 8192^3, 64 bytes to a row 212 us, this
-            // 195 us.  The stores go through a buffer resource over the tile's rows of C, or (FAR) over
-            // eight of them at a time: a row past M or a column past N addresses past its end and is dropped.
+            // accumulators (32 bytes to a row) take 308 us at 8192^3, 64 bytes to a row 212 us, 128
+            // bytes 195 us, and the 512 that the 256 x 256 tile writes in one go 193 us.  The stores go
+            // through a buffer resource over the tile's rows of C, or (FAR) over eight of them at a time: a
+            // row past M or a column past N addresses past its end and is dropped.
             // Where not even eight rows fit, 64-bit addresses.  LANES: a small tile that is its block's only
             // one, of a C whose rows are no whole number of quads: its stores are not hidden behind another
             // tile's chunks, and quads on 4-byte addresses drain slowly (2500 x 2501, K = 1000 10.75 us with

@@ -123,7 +123,7 @@ static bnn_status fc_binary_checked(const uint32_t *a_dev, int64_t m, int64_t k,
     if (st != BNN_OK) return st;
     if (!aligned16(a_dev) || !aligned16(b_dev)) return BNN_ERR_ALIGN;
     // More than 8 rows run on the matrix cores with FP32 accumulators, which hold the raw sums
-    // (at most K rounded up to a whole chunk of 2048 bits in magnitude) exactly only up to 2^24.
+    // (at most K rounded up to a whole chunk of 512 bits in magnitude) exactly only up to 2^24.
     if (m > 8 && k > FC_MFMA_MAX_K) return BNN_ERR_UNSUPPORTED;
     const int64_t tiles = ceil_div64(m, 128) * ceil_div64(n, 128);
     if (tiles > 0x7fffffffLL) return BNN_ERR_UNSUPPORTED;

@@ -122,7 +122,8 @@ int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, bool poo
 bool conv_binary_supported(int h, int w, int c_in);
 
 // Largest K of bnn_fc_binary on the matrix-core path (m > 8): K plus the zero padding to a whole
-// LDS chunk (at most 2047 bits) must not exceed 2^24, the range in which FP32 holds integers exactly.
+// LDS chunk of 512 bits must not exceed 2^24, the range in which FP32 holds integers exactly (the
+// limit leaves room for chunks of up to 2048 bits).
 constexpr int64_t FC_MFMA_MAX_K = ((int64_t)1 << 24) - 2048;
 
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }

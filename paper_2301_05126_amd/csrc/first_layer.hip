@@ -10,7 +10,7 @@
 //                     memory, the step in registers (latency: batch 1 .. 8 of a small image).
 //   conv_first_img    3x3, one ring of padding, <= 4 channels, power-of-two width: whole images
 //                     in LDS, persistent blocks (throughput: large batches of small images).
-//   conv_first_lin    kernel rows of <= 32 bytes, at most 14 16-byte units, over images of any size:
+//   conv_first_lin    up to 8 kernel rows of <= 16 bytes or 7 of <= 32, over images of any size:
 //                     256 output pixels in raster order per tile, the input rows they touch in LDS as
 //                     they lie in memory.
 //   conv_first_mfma   small kernels (kh * roundup16(kw*c_in) <= 128 bytes per pixel): the int8
@@ -1381,7 +1381,7 @@ bnn_status launch_first_img(const int8_t *in, const int8_t *wt, int n, int h, in
     return hip_result(hipGetLastError());
 }
 
-// Raster-order tiles: kernel rows of at most 32 bytes and at most 14 16-byte units in all, patches of
+// Raster-order tiles: up to eight kernel rows of at most 16 bytes or seven of at most 32, patches of
 // at most 8 KB, and less padding than the kernel is high (the input rows of consecutive output rows
 // then never run backwards from one image to the next).  BNN_ERR_UNSUPPORTED otherwise.
 template <int NG>

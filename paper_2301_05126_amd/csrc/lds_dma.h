@@ -26,8 +26,9 @@ __device__ __forceinline__ v4i make_raw_rsrc(const void *base, unsigned bytes)
 // One wave-wide copy global -> LDS without touching vector registers: lane l's 16 (or 4)
 // bytes at byte offset voff of the buffer land at LDS byte address lds_base + 16*l (4*l).
 // Written as inline assembly so that the compiler does not serialise the transfer against
-// the LDS reads of the tile being multiplied; completion is awaited explicitly
-// (s_waitcnt vmcnt(0)) before the barrier that publishes the buffer.  lds_base is wave-uniform.
+// the LDS reads of the tile being multiplied; completion is awaited explicitly before the barrier
+// that publishes the buffer, with s_waitcnt vmcnt(0) or, where younger transfers stay in flight (the
+// GEMM), vmcnt of their number.  lds_base is wave-uniform.
 // Each statement overwrites M0 and says so in its clobber list, so the compiler's own uses of M0
 // are re-initialised after it (it warns that M0 is a reserved register; that warning is silenced
 // for these four statements only).
