@@ -7,7 +7,7 @@ namespace bnn {
 #define BNN_DECL_WPH(N)                                                                                   \
     bnn_status launch_conv_binary_wph##N(const uint32_t *in, int n, int h, int w, int c_in,               \
                                          const uint32_t *wt, int c_out, const EpiArgs &ep, hipStream_t s); \
-    int conv_tile_choice_wph##N(int n, int h, int w, int c_in, int c_out, bool win, bool *raster);
+    int conv_tile_choice_wph##N(int n, int h, int w, int c_in, int c_out, bool win, bool raw, bool *raster);
 BNN_DECL_WPH(1)
 BNN_DECL_WPH(2)
 BNN_DECL_WPH(4)
@@ -33,18 +33,18 @@ static int words_per_half(int c_in)
     return wph;
 }
 
-int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, bool pooled, bool tiles_only, bool *raster)
+int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, int pool, bool tiles_only, bool *raster)
 {
     *raster = false;
     if (!conv_binary_supported(h, w, c_in) || n <= 0 || c_out <= 0) return -1;
     if (!tiles_only && conv_binary_small_qualifies(n, h, w, c_in, c_out)) return 10;
     switch (words_per_half(c_in)) {
-    case 1: return conv_tile_choice_wph1(n, h, w, c_in, c_out, pooled, raster);
-    case 2: return conv_tile_choice_wph2(n, h, w, c_in, c_out, pooled, raster);
-    case 4: return conv_tile_choice_wph4(n, h, w, c_in, c_out, pooled, raster);
-    case 6: return conv_tile_choice_wph6(n, h, w, c_in, c_out, pooled, raster);
-    case 8: return conv_tile_choice_wph8(n, h, w, c_in, c_out, pooled, raster);
-    case 16: return conv_tile_choice_wph16(n, h, w, c_in, c_out, pooled, raster);
+    case 1: return conv_tile_choice_wph1(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
+    case 2: return conv_tile_choice_wph2(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
+    case 4: return conv_tile_choice_wph4(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
+    case 6: return conv_tile_choice_wph6(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
+    case 8: return conv_tile_choice_wph8(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
+    case 16: return conv_tile_choice_wph16(n, h, w, c_in, c_out, pool == 2, pool == 0, raster);
     }
     return -1;
 }

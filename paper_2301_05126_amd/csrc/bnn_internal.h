@@ -114,9 +114,9 @@ bool conv_binary_small_qualifies(int n, int h, int w, int c_in, int c_out);
 // Which kernel a binary convolution of this shape runs on (host-side query, launches nothing):
 // 10 = small-problem kernel, 3 = 256 x 128 block tile, 2 = 128 x 128 with streamed weights,
 // 1 = 128 x 128, 4 = 256 x 64, 5 = 128 x 64, 0 = 64 x 64, -1 = unsupported shape.
-// pooled: a layer with pooling (its tiles are made of windows, which may decide otherwise).
+// pool: 1 or 2 (tiles of a pooled layer are made of windows, which may decide otherwise), 0 = raw sums alone.
 // tiles_only: as launch_conv_binary_tiles.  *raster: tiles in raster order, not rectangles.
-int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, bool pooled, bool tiles_only, bool *raster);
+int conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, int pool, bool tiles_only, bool *raster);
 
 // Whether launch_conv_binary can run this shape (LDS budget of the input patch).
 bool conv_binary_supported(int h, int w, int c_in);

@@ -81,7 +81,7 @@ TILE_256x64, TILE_128x64 = 4, 5
 
 def conv_kernel_tiling(n, h, w, c_in, c_out, pool=1, tiles_only=False):
     """(kernel, raster order) that a binary convolution of this shape runs on (host-side query, no GPU
-    work); a pooled layer may differ from an unpooled one."""
+    work); pool 1, 2 or 0 = raw sums alone, which may differ."""
     import ctypes as C
     raster = C.c_int(-1)
     choice = hooks().bnn_test_conv_binary_kernel_choice(n, h, w, c_in, c_out, pool, 1 if tiles_only else 0,

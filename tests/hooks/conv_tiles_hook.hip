@@ -20,12 +20,12 @@ extern "C" bnn_status bnn_test_conv_binary_tiles(const uint32_t *in_dev, int n, 
 // Which kernel bnn_conv_binary (tiles_only == 0) or the hook above (tiles_only != 0) runs a shape
 // on: 10 = small-problem kernel, 3 = 256 x 128 tile, 2 = 128 x 128 tile with streamed weights,
 // 1 = 128 x 128, 4 = 256 x 64, 5 = 128 x 64, 0 = 64 x 64, -1 = unsupported; *raster: its tiles are in raster
-// order, not rectangles.  Host-only.
+// order, not rectangles.  pool: 1, 2 or 0 = raw sums alone.  Host-only.
 extern "C" int bnn_test_conv_binary_kernel_choice(int n, int h, int w, int c_in, int c_out, int pool, int tiles_only,
                                                   int *raster)
 {
     bool r = false;
-    const int choice = bnn::conv_binary_kernel_choice(n, h, w, c_in, c_out, pool == 2, tiles_only != 0, &r);
+    const int choice = bnn::conv_binary_kernel_choice(n, h, w, c_in, c_out, pool, tiles_only != 0, &r);
     *raster = r ? 1 : 0;
     return choice;
 }

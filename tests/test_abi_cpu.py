@@ -199,6 +199,9 @@ def test_kernel_choice_of_the_benchmark_shapes(lib):
     for hw, c in W.CONV_SWEEP_SHAPES:
         assert conv_kernel_choice(1024, hw, hw, c, c) in (TILE_256x128, 1, 2)
     assert conv_kernel_choice(4, 8, 8, 2048, 32) == -1       # more than 1024 channels: unsupported
+    for n, h, w, ci, co in [(961, 10, 31, 64, 100), (941, 15, 15, 64, 155), (412, 18, 18, 128, 268)]:
+        assert conv_kernel_choice(n, h, w, ci, co) == TILE_256x128
+        assert conv_kernel_choice(n, h, w, ci, co, pool=0) != TILE_256x128       # raw sums: mostly stores
 
 
 def test_lds_opt_in_is_per_device(lib):
