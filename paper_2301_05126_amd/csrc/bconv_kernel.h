@@ -862,9 +862,9 @@ namespace {
 // short for them to matter.)
 template <int WPH> constexpr bool narrow_tiles = WPH == 2 || WPH == 4 || WPH == 6;
 
-// Which block tile launch_wph takes: the one of least estimated cost.  Over 219 layers it takes 1.7 % more
-// than the fastest tile and tiling on average and 5 % more for 26 of them; furthest off are layers that
-// keep few MFMAs in flight (578 x 28 x 14, 384 -> 192 pooled 81 / 61 with 256 x 64, 1431 x 8 x 8, 192 -> 256
+// Which block tile launch_wph takes: the one of least estimated cost.  Over 219 layers (raw sums without the
+// rule below) it takes 1.7 % more than the fastest tile and tiling on average and 5 % more for 26 of them;
+// furthest off are layers that keep few MFMAs in flight (578 x 28 x 14, 384 -> 192 pooled 81 / 61 with 256 x 64, 1431 x 8 x 8, 192 -> 256
 // 29.1 / 24.7 with 128 x 128).  The largest tile, which moves the least data, stays where it gives nearly
 // every compute unit two blocks unless another promises 10 % less (without that 598 x 28 x 28, 64 -> 48
 // 21.3 -> 27.1, 305 x 21 x 21, 448 -> 149 66.6 -> 80.3).
@@ -873,11 +873,12 @@ template <int WPH> constexpr bool narrow_tiles = WPH == 2 || WPH == 4 || WPH == 
 // 17.0 / 9.2 (64 x 64).
 // 3: 256 x 128, 2: 128 x 128 with streamed weights, 1: 128 x 128, 4: 256 x 64, 5: 128 x 64,
 // 0: 64 x 64.  win: a pooled layer (its tiles are made of 2x2 windows).  *raster: linear tiles.
-// raw: raw sums alone.  They are mostly stores up to 256 channels, which a block overlaps with another's
-// multiplies only: smaller tiles (us, 256 x 128 rectangles / raster / 128 x 128: 961 x 10 x 31, 64 -> 100 39.8 / 42.7 /
-// 34.6, 941 x 15 x 15, 64 -> 155 129.5 / 146.0 / 129.5, 412 x 18 x 18, 128 -> 268 89.1 / 54.2 / 47.4, 160 x 17 x 24, 160 ->
-// 328 62.9 / 41.3 / 37.3; over 49 layers the 128 x 128 tile is at most 2 % slower where 256 x 128 was taken, but
-// for 589 x 31 x 31, 64 -> 56).
+// raw: raw sums alone.  They are mostly stores up to 256 channels, which the estimate leaves out and a block
+// overlaps with another's multiplies only: smaller tiles.  us, with the largest tile allowed / without:
+// 961 x 10 x 31, 64 -> 100 39.2 / 32.9, 941 x 15 x 15, 64 -> 155 145.4 / 129.7, 127 x 26 x 26, 64 -> 171
+// 78.0 / 61.3, 589 x 31 x 31, 64 -> 56 47.4 / 39.9; 1.067 times as fast over 49 layers.  Slower are
+// 450 x 20 x 20, 32 -> 188 39.3 / 41.4, 543 x 25 x 25, 128 -> 104 41.0 / 42.3, 192 x 18 x 18, 48 -> 372
+// 25.0 / 25.7, 160 x 17 x 24, 160 -> 328 33.6 / 34.6.
 template <int WPH>
 int tile_choice_wph(int n, int h, int w, int c_in, int c_out, bool win, bool raw, bool *raster = nullptr)
 {
